@@ -19,7 +19,7 @@
 //
 // Arithmetic of the weights.  P is rounded to fp16 (11 significant bits) and V^T arrives as fp16 from the states
 // kernel (bf16 or E4M3 values are exact in fp16 once divided by the power of two the states kernel picks per key
-// block; its base-2 logarithm comes in `lvs` and is added to the exponent of the weights, so the product is
+// block; its base-2 logarithm comes in `vks` and is added to the exponent of the weights, so the product is
 // unchanged).  The second product runs on the fp16 MFMA at the rate of the bf16 one with an eighth of the rounding
 // error on the weights.  That margin pays for a running maximum that is only raised when a lane sees an exponent
 // above kRaise: the accumulators are rescaled a few times per row instead of once per tile, and the softmax of a
@@ -31,12 +31,19 @@
 // value pins below hold the order).  Everything with control flow (raising the maximum, the first unit of a row, a
 // ragged key block, a key block whose V scale is far below the first one's) sits between the steps or in the
 // "careful" variant of a step.  In the middle of a list, where none of the special cases can occur (one bit per list
-// entry says so), iterations run three at a time in a form without guards.
+// entry says so), iterations run in a form without guards, and, where |q| max|k| bounds the exponents of the wave's rows,
+// without looking at the maximum at all.  What bounds the kernel: the issue of vector instructions beside the MFMA (326
+// cycles for a unit's instructions in a register-only loop at two waves per SIMD, 256 of them MFMA), and on long bf16
+// launches the clock the chip grants (1.5 GHz).  Without the overflow checks and the dot-product row sums, at two ring
+// slots for 64-row blocks: 16 heads x 10992 tokens, lists of 9: 74 -> 61 us; 43968 tokens, lists of 34, bf16: 0.60 -> 0.54 ms;
+// 137400 tokens, lists of 64, e4m3: 2.54 -> 2.35 ms.
 //
 // Memory pipeline.  K and V^T tiles go from global memory straight into LDS (global_load_lds_dwordx4, no staging
-// registers) into two rings of three slots each.  K runs ahead of V^T by the pipeline's skew, so the copies of an
-// iteration are needed two iterations later; one workgroup barrier per tile publishes what has landed and frees
-// the slots that were consumed.  Rows are stored unpadded with the 16-byte chunk index XOR-ed by row bits (applied
+// registers) into two rings of SL slots each.  K runs ahead of V^T by the pipeline's skew, so the copies of an
+// iteration are needed SL - 1 iterations later; one workgroup barrier per tile publishes what has landed and frees
+// the slots that were consumed.  Three slots for 128-row blocks (two workgroups of four waves fill a CU's registers, 49 KB
+// each); two for 64-row blocks, so that four workgroups of two waves fit a CU's LDS (three slots: three workgroups, six
+// waves instead of eight).  Rows are stored unpadded with the 16-byte chunk index XOR-ed by row bits (applied
 // on the global side of the copy), which keeps the fragment reads free of bank conflicts.  The copies are inline
 // assembly, invisible to the compiler's wait-count insertion, and are awaited by explicit s_waitcnt vmcnt(n).
 //
@@ -64,6 +71,11 @@ constexpr float kRaise = 12.0f;
 // of fp16, so its row sums are formed in fp32.
 constexpr float kTinyV = 8.0f;
 
+// Rows whose exponents are bounded skip the overflow check (see bounded_rows below): weights at most 2^kTopW, at most
+// kDrop binades below their place under the exact maximum of the units seen so far.
+constexpr float kTopW = 15.0f;
+constexpr float kDrop = 6.0f;
+
 typedef __attribute__((address_space(3))) void *lds_void_p;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
@@ -86,23 +98,24 @@ template <int N> __device__ __forceinline__ void wait_copies_and_barrier()
 #endif
 }
 
-// N such copies from the same base to consecutive kilobytes of LDS (per-lane offsets voff[0..N-1]) in one statement
-template <int N> __device__ __forceinline__ void copy_nk_to_lds(const uint8_t *base, const int (&voff)[N], uint32_t lds_addr)
+// Two such copies, from base0 + v0 and base1 + v1, to consecutive kilobytes of LDS in one statement
+__device__ __forceinline__ void copy_2k_to_lds(const uint8_t *base0, const uint8_t *base1, uint32_t v0, uint32_t v1, uint32_t lds_addr)
+{
+    uint32_t saved_m0;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\t"
+                 "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %4\n\ts_mov_b32 m0, %0"
+                 : "=&s"(saved_m0) : "v"(v0), "v"(v1), "s"(base0), "s"(base1), "s"(lds_addr) : "memory", "scc");
+}
+// N such copies of consecutive 1 KB pieces of a tile: piece x starts at base + x stride in memory and takes the per-lane
+// offset voff, for odd x with bit 6 flipped if FLIP (see CopyOffsets)
+template <int N, bool FLIP> __device__ __forceinline__ void copy_nk_to_lds(const uint8_t *base, uint32_t stride, uint32_t voff, uint32_t lds_addr)
 {
     static_assert(N == 1 || N == 2 || N == 4, "1, 2 or 4 copies");
-    uint32_t saved_m0;
-    if constexpr (N == 1) {
-        copy_1k_to_lds(base, voff[0], lds_addr);
-    } else if constexpr (N == 2) {
-        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\t"
-                     "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
-                     : "=&s"(saved_m0) : "v"(voff[0]), "v"(voff[1]), "s"(base), "s"(lds_addr) : "memory", "scc");
-    } else {
-        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %6\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %5\n\t"
-                     "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %5\n\t"
-                     "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %5\n\t"
-                     "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %5\n\ts_mov_b32 m0, %0"
-                     : "=&s"(saved_m0) : "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(base), "s"(lds_addr) : "memory", "scc");
+    if constexpr (N == 1) copy_1k_to_lds(base, voff, lds_addr);
+    else {
+        const uint32_t odd = FLIP ? voff ^ 64u : voff;
+#pragma unroll
+        for (int x = 0; x < N; x += 2) copy_2k_to_lds(base + x * stride, base + (x + 1) * stride, voff, odd, lds_addr + x * 1024);
     }
 }
 
@@ -145,26 +158,57 @@ struct Tile {
     static constexpr int LDS = WOFF + (FP8 ? 8192 : 0);
 };
 
-// Per-lane byte offsets (inside a tile) of the 16-byte chunk each lane copies, one per copy
-// instruction of this wave: LDS position (row, slot) <- global chunk slot ^ swizzle(row).
+// The lane index, computed here (two instructions) and not carried in a register from the top of the kernel
+__device__ __forceinline__ int lane_now()
+{
+    int l = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    asm volatile("" : "+v"(l));
+    return l;
+}
+
+// Per-lane byte offset of the 16-byte chunk each lane copies in one 1 KB instruction: LDS position (row, slot) <- global
+// chunk slot ^ swizzle(row).  Instruction `ins` of a tile covers rows 8 ins .. (128-byte rows) or 16 ins .. (64-byte rows),
+// which advances the swizzle by 4 ins mod 8 (a flip of offset bit 6 for odd ins) or by 4 ins mod 4 = 0: one register
+// serves all of a wave's copies, the rows themselves are advanced in the scalar base (row pitches are multiples of 128 bytes
+// where the flip is used).
 template <int NWAVES, bool FP8>
 struct CopyOffsets {
     using T = Tile<NWAVES, FP8>;
-    int k[T::KINS], v[T::VINS];
-    int krow[T::KINS];            // K row of this lane per instruction (for clamping at a ragged end)
+    static constexpr int kRows = FP8 ? 16 : 8;         // K rows per instruction
+    uint32_t k, v;
+    uint32_t kstride;                                  // bytes from one K instruction's rows to the next's (uniform)
+    int wave_k, wave_v;                                // first instruction of this wave (uniform)
     // krowb: bytes between consecutive K rows in global memory (64 or 128 when the heads are contiguous)
-    __device__ __forceinline__ void init(int wave, int lane, int krowb)
+    __device__ __forceinline__ void init(int wave_u, int lane, int krowb)
     {
+        wave_k = wave_u * T::KINS;
+        wave_v = wave_u * T::VINS;
+        kstride = (uint32_t)kRows * (uint32_t)krowb;
+        const uint32_t r = lane >> 3, chunk = (uint32_t)((lane & 7) ^ swz8(r)) << 4;
+        v = r * 128u + chunk;
+        k = FP8 ? (uint32_t)(lane >> 2) * (uint32_t)krowb + ((uint32_t)((lane & 3) ^ swz4(lane >> 2)) << 4) : r * (uint32_t)krowb + chunk;
+        if constexpr (T::KINS == 1 && !FP8) k ^= (uint32_t)(wave_k & 1) << 6;
+        if constexpr (T::VINS == 1) v ^= (uint32_t)(wave_v & 1) << 6;
+    }
+    // this wave's share of the K tile at kt / of a contiguous 8 KB tile at vt, to the tile at LDS address dst
+    __device__ __forceinline__ void copy_k(const uint8_t *kt, uint32_t dst) const
+    {
+        copy_nk_to_lds<T::KINS, !FP8>(kt + wave_k * kstride, kstride, k, dst + wave_k * 1024);
+    }
+    __device__ __forceinline__ void copy_v(const uint8_t *vt, uint32_t dst) const
+    {
+        copy_nk_to_lds<T::VINS, true>(vt + wave_v * 1024, 1024u, v, dst + wave_v * 1024);
+    }
+    // the K tile of the ragged last block: rows past the end are clamped to the last one (they are masked later)
+    __device__ __forceinline__ void copy_k_ragged(const uint8_t *kt, uint32_t dst, int rows, int krowb) const
+    {
+        const int lane = lane_now();
 #pragma unroll
         for (int x = 0; x < T::KINS; ++x) {
-            const int ins = wave * T::KINS + x;
-            if (FP8) { const int r = ins * 16 + (lane >> 2); krow[x] = r; k[x] = r * krowb + (((lane & 3) ^ swz4(r)) << 4); }
-            else     { const int r = ins * 8 + (lane >> 3);  krow[x] = r; k[x] = r * krowb + (((lane & 7) ^ swz8(r)) << 4); }
-        }
-#pragma unroll
-        for (int x = 0; x < T::VINS; ++x) {
-            const int ins = wave * T::VINS + x, r = ins * 8 + (lane >> 3);
-            v[x] = r * 128 + (((lane & 7) ^ swz8(r)) << 4);
+            const int row = (wave_k + x) * kRows + (lane >> (FP8 ? 2 : 3));
+            // (offsets from the tile's first row: a lane offset is unsigned, the clamped row may lie before this instruction's first)
+            const uint32_t off = (k ^ ((!FP8 && (x & 1)) ? 64u : 0u)) + (uint32_t)((wave_k + x) * (int)kstride - (row - min(row, rows - 1)) * krowb);
+            copy_1k_to_lds(kt, off, dst + (wave_k + x) * 1024);
         }
     }
 };
@@ -182,24 +226,24 @@ __device__ unsigned long long sla_probe_times[64 * 8];
 #endif
 
 // NW: 32-row query groups per workgroup (query block = 32 NW rows), one wave per group.
-// SL: ring slots (three: the pipeline described above).
+// SL: ring slots (two or three, see above).
 template <int NW, bool FP8, int SL>
 __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
-    const void *__restrict__ Qp, const void *__restrict__ Kp, const uint16_t *__restrict__ Vp, const float *__restrict__ lvs,
+    const void *__restrict__ Qp, const void *__restrict__ Kp, const uint16_t *__restrict__ Vp, const float2 *__restrict__ vks,
     const float *__restrict__ sQ, const float *__restrict__ sK, RowMap rm,
     const int32_t *__restrict__ crit_idx, int k_c, const uint16_t *__restrict__ Hq, const uint16_t *__restrict__ WT,
     int proj_per_head, int phi, int H, int N, int Nqb, int Nkb, long total, float c_exp, uint16_t *__restrict__ O, float *__restrict__ O32)
 {
     constexpr int NWAVES = NW;
     using T = Tile<NWAVES, FP8, SL>;
-    static_assert(SL == 3, "the pipeline below needs three ring slots");
+    static_assert(SL == 2 || SL == 3, "ring slots");
     constexpr int BQ = 32 * NW;
     constexpr int ES = FP8 ? 1 : 2;                     // bytes per input element
     constexpr int KROWB = FP8 ? 64 : 128;               // bytes of a K row in LDS
     __shared__ __attribute__((aligned(1024))) uint8_t lds[T::LDS];
     // All kernel arguments are fetched here, in one batch of scalar loads: left to the compiler each would be loaded in
     // front of its first use, a dozen scalar-cache round trips one after the other along the prologue and the epilogue.
-    asm volatile("" ::"s"(Qp), "s"(Kp), "s"(Vp), "s"(lvs), "s"(sQ), "s"(sK), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(crit_idx),
+    asm volatile("" ::"s"(Qp), "s"(Kp), "s"(Vp), "s"(vks), "s"(sQ), "s"(sK), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(crit_idx),
                  "s"(k_c), "s"(Hq), "s"(WT), "s"(proj_per_head), "s"(phi), "s"(H), "s"(N), "s"(Nqb), "s"(Nkb), "s"(total), "s"(c_exp), "s"(O), "s"(O32));
     const long work = xcd_remap(blockIdx.x, total);
     if (work >= total) return;                        // the whole workgroup leaves together
@@ -223,7 +267,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     const int krowb = rm.ts * ES;                     // bytes between consecutive K rows
     const uint8_t *Kh = (const uint8_t *)Kp + head * ES;
     const uint8_t *Vh = (const uint8_t *)(Vp + (size_t)bh * Nkb * kBK * kD);
-    const float *lvh = lvs + bh * Nkb;
+    const float2 *vkh = vks + bh * Nkb;
 
     SLA_TP(62, 0);
     // The critical list of the row is asked for first of all: the tile copies, the scale gather and with them the whole
@@ -265,10 +309,19 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
 #pragma unroll
     for (int x = 0; x < 16; ++x) zero16[x] = 0.f;
     f32x16 oacc[2] = {zero16, zero16};
-    // Running state of the lane's row.  m_run: reference exponent (log2 domain) of the weights; l_part: this lane's
-    // share of the row sum, accumulated from the fp16 weights the second product consumes (divided by the V scale
-    // ratio again); l_full: row sums formed in fp32 by the careful steps (already complete over the lane pair).
-    float m_run = -INFINITY, l_part = 0.f, l_alt = 0.f, l_full = 0.f;      // (l_alt: second partial sum of the fast steps)
+    // Running state of the lane's row.  m_run: reference exponent (log2 domain) of the weights; lsum: the row sum,
+    // accumulated from the fp16 weights the second product consumes (divided by the V scale ratio again); l_full: row sums formed in fp32 by the careful steps (already complete over the lane pair).
+    float m_run = -INFINITY, l_full = 0.f;
+    // The row sums of the fast steps come from the matrix unit: A holds 1 / (V scale ratio) where row i = lane % 16 and the
+    // 8-weight chunk lane / 16 of K belong together -- i % 4 == 0 and (i / 4) % 2 == chunk % 2 -- and 0 elsewhere, so that
+    // row 0 (8) adds the chunks of queries 0..15 and row 4 (12) those of queries 16..31 of the P operand, and register 0 of
+    // every lane ends up with the sum of its own query row, both lanes of the pair included.  (Eight v_dot2 per unit, the
+    // obvious way, run on the matrix unit as well: 20 cycles each, 160 beside the unit's 256; two of these take 32.  In a
+    // register-only loop of a unit's instructions at two waves per SIMD: 407 cycles with the dot products, 371 with sixteen
+    // adds, 354 with two 32x32 products of ones, 326 with these.)
+    f32x4 lsum = {0.f, 0.f, 0.f, 0.f};
+    const uint32_t ones_mask = ((lane & 3) == 0 && (((lane >> 2) ^ (lane >> 4)) & 1) == 0) ? ~0u : 0u;
+    f16x8 ones;
 
     // Ragged block: only the last key block of the sequence can be short.
     const int tail_rows = N & (kBK - 1), ragged_j = tail_rows ? Nkb - 1 : -1;
@@ -302,15 +355,21 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     }
     // the scales of the window's blocks: a gather that depends on the indices (the first tile copies are requested
     // between the two, see the prologue)
+    // w_kc, w_lv: over the window's valid entries, the largest |K row| times exp2 constant and the largest log2 V scale
+    // relative to the first tile's.  |q| w_kc + w_lv bounds the exponent of every weight of a row (Cauchy-Schwarz).
+    float w_kc = 0.f, w_lv = 0.f;
     auto load_window_scales = [&](bool first) __attribute__((always_inline)) {
-        float lv = lvh[d_j];
+        float2 vk = vkh[d_j];
         // exp2 constant of the tile: softmax scale * log2(e) (* Q and K block scales for e4m3)
         d_cj = FP8 ? fmaxf(c_exp * qscale * sK[bh * Nkb + d_j], 1e-30f) : c_exp;
-        asm volatile("" : "+v"(lv), "+v"(d_cj));       // the loads complete here, not at some later first use
+        asm volatile("" : "+v"(vk.x), "+v"(vk.y), "+v"(d_cj));       // the loads complete here, not at some later first use
         // log2 of the V scale of the first tile: the reference of the weights
-        if (first) lv_ref = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(lv)));
-        d_lv = lv - lv_ref;
-        d_bad = __ballot(wbase + lane >= k || d_j == ragged_j || !(fabsf(d_lv) <= kTinyV));
+        if (first) lv_ref = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(vk.x)));
+        d_lv = vk.x - lv_ref;
+        const bool in = wbase + lane < k;
+        d_bad = __ballot(!in || d_j == ragged_j || !(fabsf(d_lv) <= kTinyV));
+        w_kc = wave_max_dpp(in ? vk.y * d_cj : 0.f);
+        w_lv = wave_max_dpp(in ? d_lv : -INFINITY);
     };
     auto load_window = [&](int wb) __attribute__((always_inline)) {
         const int idx = wb + lane;
@@ -323,32 +382,26 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
 
     SLA_TP(62, 1);
     CopyOffsets<NWAVES, FP8> co;
-    co.init(wave, lane, krowb);
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);                       // same value, provably uniform
+    co.init(wave_u, lane, krowb);
     const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_void_p)lds;                // LDS byte address of the K ring
     const uint32_t ktile_bytes = (uint32_t)kBK * (uint32_t)krowb;                  // bytes from one K block to the next
-    const uint32_t kdst0 = lds_base + wave_u * T::KINS * 1024, vdst0 = lds_base + T::VRING + wave_u * T::VINS * 1024;
     // slot: byte offset of the ring slot (a multiple of the tile size below 3 tiles)
-    auto request_K = [&](int c, uint32_t slot, bool full = false) __attribute__((always_inline)) {       // K tile of list entry c into the slot at byte offset `slot` of the K ring (full: known not to be the ragged block)
+    auto request_K = [&](int c, uint32_t slot) __attribute__((always_inline)) {       // K tile of list entry c into the slot at byte offset `slot` of the K ring
 #ifdef SLA_PROBE_NOCOPY
         return;
 #endif
         const uint32_t j = (uint32_t)entry_j(c);
         const uint8_t *kt = Kh + (uint64_t)j * ktile_bytes;
-        if (full || (int)j != ragged_j) {
-            copy_nk_to_lds<T::KINS>(kt, co.k, kdst0 + slot);
-        } else {                                       // rows past the end are clamped to the last one; they are masked later
-#pragma unroll
-            for (int x = 0; x < T::KINS; ++x)
-                copy_1k_to_lds(kt, co.k[x] - (co.krow[x] - min(co.krow[x], tail_rows - 1)) * krowb, kdst0 + slot + x * 1024);
-        }
+        if ((int)j != ragged_j) co.copy_k(kt, lds_base + slot);
+        else co.copy_k_ragged(kt, lds_base + slot, tail_rows, krowb);
     };
     auto request_V = [&](int c, uint32_t slot) __attribute__((always_inline)) {       // V^T tile of list entry c into the slot at byte offset `slot` of the V^T ring
 #ifdef SLA_PROBE_NOCOPY
         return;
 #endif
         const uint8_t *vt = Vh + (uint64_t)(uint32_t)entry_j(c) * (uint32_t)(kBK * kD * 2);
-        copy_nk_to_lds<T::VINS>(vt, co.v, vdst0 + slot);
+        co.copy_v(vt, lds_base + T::VRING + slot);
     };
     // The operands of the linear/projection epilogue (the 64x64 tile of Hq^T, the Z row, W^T) travel the same way
     // into the K ring, which is idle during the last tile, so their latency hides behind that tile's arithmetic.
@@ -357,22 +410,30 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     constexpr int kHqOff = 0, kWtOff = FP8 ? T::WOFF : 8192;
     auto request_epilogue = [&]() __attribute__((always_inline)) {
         if (Hq == nullptr) return;
-#pragma unroll
-        for (int x = 0; x < T::VINS; ++x) copy_1k_to_lds(Hi8, co.v[x], lds_base + kHqOff + (wave_u * T::VINS + x) * 1024);
-#pragma unroll
-        for (int x = 0; x < T::VINS; ++x) copy_1k_to_lds(Wh8, co.v[x], lds_base + kWtOff + (wave_u * T::VINS + x) * 1024);
-        if (tid < 8) copy_1k_to_lds(Hi8 + 64 * kD * 2, tid * 16, lds_base + T::ZOFF);   // Z: 128 bytes, 8 lanes of wave 0
+        co.copy_v(Hi8, lds_base + kHqOff);
+        co.copy_v(Wh8, lds_base + kWtOff);
+        const int ln = lane_now();
+        if (wave_u == 0 && ln < 8) copy_1k_to_lds(Hi8 + 64 * kD * 2, ln * 16, lds_base + T::ZOFF);   // Z: 128 bytes, 8 lanes of wave 0
     };
 
     // ---- per-tile constants (wave-uniform)
-    struct TileInfo { int valid; float cj, lsv, invr; bool tiny; };
+    struct TileInfo { int valid; float cj, lsv; uint32_t inv2; bool tiny; };
+    // 2^-lsv as two fp16 in a scalar register
+    auto inv2_of = [&](float lsv) __attribute__((always_inline)) {
+        const float r = fast_exp2(-lsv);
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)pack_f16(r, r));
+    };
+    auto set_ones = [&](uint32_t inv2) __attribute__((always_inline)) {
+        const uint32_t w = ones_mask & inv2;
+        ones = __builtin_bit_cast(f16x8, make_uint4(w, w, w, w));
+    };
     auto tile_info = [&](int c) __attribute__((always_inline)) {
         TileInfo t;
         t.valid = entry_j(c) == ragged_j ? tail_rows : kBK;
         t.cj = FP8 ? __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(d_cj), c - wbase)) : c_exp;
         t.lsv = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(d_lv), c - wbase));   // the V scale of the tile rides on the weights: P' = P * 2^lsv
         t.tiny = fabsf(t.lsv) > kTinyV;
-        t.invr = fast_exp2(-t.lsv);                    // and is divided out of the row sums again
+        t.inv2 = inv2_of(t.lsv);                       // and is divided out of the row sums again
         return t;
     };
 
@@ -432,24 +493,19 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
         }
         return s;
     };
-    // O^T += V^T P^T of one unit, and the lane's share of its row sums from the same fp16 weights
-    struct Weights { f16x8 p[2]; float invr; };        // invr = 0: the row sums of this unit were formed elsewhere
+    // O^T += V^T P^T of one unit, and its row sums from the same fp16 weights
+    struct Weights { f16x8 p[2]; uint32_t inv2; };     // inv2 = 0: the row sums of this unit were formed elsewhere
     auto accumulate = [&](const VFrag &vf, const Weights &w) __attribute__((always_inline)) {
-        const f16x2 iv = {(_Float16)w.invr, (_Float16)w.invr};
+        set_ones(w.inv2);
 #pragma unroll
         for (int ss = 0; ss < 2; ++ss) {
 #pragma unroll
             for (int e = 0; e < 2; ++e) oacc[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf.f[ss][e], w.p[ss], oacc[e], 0, 0, 0);
-            const uint4 pw = __builtin_bit_cast(uint4, w.p[ss]);
-            l_part = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, pw.x), iv, l_part, false);
-            l_part = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, pw.y), iv, l_part, false);
-            l_part = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, pw.z), iv, l_part, false);
-            l_part = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, pw.w), iv, l_part, false);
+            lsum = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, w.p[ss], lsum, 0, 0, 0);
         }
     };
     auto rescale = [&](float alpha) __attribute__((always_inline)) {
-        l_part *= alpha;
-        l_alt *= alpha;
+        lsum[0] *= alpha;
         l_full *= alpha;
 #pragma unroll
         for (int e = 0; e < 2; ++e)
@@ -477,16 +533,16 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
         l_full += sum + xchg32(sum);
         w.p[0] = pack8_f16(s, 0);
         w.p[1] = pack8_f16(s, 8);
-        w.invr = 0.f;
+        w.inv2 = 0u;
     };
 
     // ---- prologue: the first copies, Q, and S^T of unit 0
     if (k == 0) request_epilogue();
     if (k > 0) request_K(0, 0);
     if (k > 1) request_K(1, T::KBYTES);
-    if (k > 2) request_K(2, 2 * T::KBYTES);
+    if (SL > 2 && k > 2) request_K(2, 2 * T::KBYTES);
     if (k > 0) request_V(0, 0);
-    if (k > 1) request_V(1, T::VBYTES);
+    if (SL > 2 && k > 1) request_V(1, T::VBYTES);
     SLA_TP(62, 2);
     load_window_scales(true);
     // Let the Q fragments (ordinary loads the compiler tracks) and the first tiles land here, once: left to the
@@ -505,11 +561,27 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     f32x16 s_cur = zero16;
     Weights w_prev;
     w_prev.p[0] = w_prev.p[1] = __builtin_bit_cast(f16x8, make_uint4(0, 0, 0, 0));
-    w_prev.invr = 0.f;
-    KFrag kf_use, kf_pre;
+    w_prev.inv2 = 0u;
+    KFrag kf_use;
     VFrag vf_use, vf_pre;
     TileInfo t_cur, t_nxt;
     const int U = 2 * k;                               // units of this wave
+    // norm of the lane's query row, from above (e4m3: of the codes, the scale is in the tile's exp2 constant)
+    float qnorm = 0.f;
+    if (FP8) {
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {
+            const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8(q8[w], false), hi = __builtin_amdgcn_cvt_pk_f32_fp8(q8[w], true);
+            qnorm = fmaf(lo[0], lo[0], fmaf(lo[1], lo[1], fmaf(hi[0], hi[0], fmaf(hi[1], hi[1], qnorm))));
+        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const uint4 w = __builtin_bit_cast(uint4, qf[s]);
+            qnorm = dot2_bf16(w.x, w.x, dot2_bf16(w.y, w.y, dot2_bf16(w.z, w.z, dot2_bf16(w.w, w.w, qnorm))));
+        }
+    }
+    qnorm = norm_from_above(qnorm + xchg32(qnorm));
     if (k > 0) {
         t_cur = tile_info(0);
         s_cur = compute_S(load_kfrag(0, unit_half(0)), t_cur.valid == kBK ? zero16 : s_init(t_cur.valid, unit_half(0)));
@@ -534,12 +606,12 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
         f32x16 s_nxt = zero16;
         Weights w;
         vf_pre = load_vfrag(cv, hv);                   // always in bounds (a slot of the ring); unused if there is no such step
-        kf_pre = load_kfrag(ck, hk);
         if (has_pv) accumulate(vf_use, w_prev);
         if (has_s) s_nxt = compute_S(kf_use, tn.valid == kBK ? zero16 : s_init(tn.valid, half_n));
+        kf_use = load_kfrag(ck, hk);
         softmax_careful(s_cur, t, w);
         over_cur = has_s ? overflows(s_nxt, tn) : true;
-        s_cur = s_nxt; w_prev = w; vf_use = vf_pre; kf_use = kf_pre;
+        s_cur = s_nxt; w_prev = w; vf_use = vf_pre;
     };
     // Fast form (a unit in the middle of the list, full tiles, no exponent above kRaise), written out in issue order:
     // one MFMA, then a share of the vector work (staggered: exponentials of one pair of weights, the pack of the pair
@@ -550,12 +622,10 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     // that open a new accumulator at the end of the block, and the exponentials behind them), and in a scheduling
     // barrier for the later passes.  The running maximum stays where it is.  The step ends with the overflow check of
     // the next unit, while the last MFMA runs.
-    auto fast_step = [&](const TileInfo &t, const TileInfo &tn, int cv, int hv, int ck, int hk) __attribute__((always_inline)) {
+    auto fast_step = [&](bool checked, const TileInfo &t, const TileInfo &tn, int cv, int hv, int ck, int hk) __attribute__((always_inline)) {
         f32x16 s_nxt = zero16;
         Weights w;
         vf_pre = load_vfrag(cv, hv);
-        kf_pre = load_kfrag(ck, hk);
-        const f16x2 iv = {(_Float16)w_prev.invr, (_Float16)w_prev.invr};
         uint32_t pw[8];
         float moff = t.lsv - m_run;
         auto pv = [&](int ss, int e) { oacc[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf_use.f[ss][e], w_prev.p[ss], oacc[e], 0, 0, 0); };
@@ -578,68 +648,70 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
             for (int x = x0; x <= x1; ++x) s_cur[x] = fast_exp2(s_cur[x]);
         };
         auto cv2 = [&](int pr) { pw[pr] = pack_f16(s_cur[2 * pr], s_cur[2 * pr + 1]); };
-        auto dots = [&](int ss) {
-            const uint4 q4 = __builtin_bit_cast(uint4, w_prev.p[ss]);
-            l_part = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, q4.x), iv, l_part, false);
-            l_alt = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, q4.y), iv, l_alt, false);
-            l_part = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, q4.z), iv, l_part, false);
-            l_alt = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, q4.w), iv, l_alt, false);
-        };
+        auto rs = [&](int ss) { lsum = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, w_prev.p[ss], lsum, 0, 0, 0); };
         SLA_SB();
         if (!FP8) {
-            // S^T of the next unit first: its last MFMA then has four more behind it before the step ends with the
+            // S^T of the next unit first: its last MFMA then has six more behind it before the step ends with the
             // overflow check on its result (and the next step starts with its exponentials)
-            // the vector work of a share is staggered: the exponentials of pair i, the pack of pair i-1 (whose
-            // exponentials have left the quarter-rate pipe by now) and the multiply-adds of pair i+1
-            fm(0, 1);
-            sm(0);    ex(0, 1);   fm(2, 3);
+            // the vector work is staggered: a pair's exponentials, its pack two or three instructions later (the
+            // exponentials have left the quarter-rate pipe by then), multiply-adds two or three values ahead; four
+            // instructions to a share, of which the ten MFMA take 32 (the row sums 16) cycles each
+            fm(0, 2);
+            sm(0);    ex(0, 1);   fm(3, 4);
             SLA_PIN("+v"(s_nxt), "+v"(moff)); SLA_SB();
-            sm(1);    ex(2, 3);   cv2(0); fm(4, 5);
+            sm(1);    ex(2, 3);   cv2(0); fm(5, 5);
             SLA_PIN("+v"(s_nxt), "+v"(moff), "+v"(pw[0])); SLA_SB();
-            sm(2);    ex(4, 5);   cv2(1); fm(6, 7);
+            sm(2);    ex(4, 5);   cv2(1); fm(6, 6);
             SLA_PIN("+v"(s_nxt), "+v"(moff), "+v"(pw[1])); SLA_SB();
-            sm(3);    ex(6, 7);   cv2(2); fm(8, 9);
+            sm(3);    ex(6, 6);   fm(7, 7); cv2(2); fm(8, 8);
             SLA_PIN("+v"(s_nxt), "+v"(moff), "+v"(pw[2])); SLA_SB();
-            pv(0, 0); ex(8, 9);   cv2(3); fm(10, 11);
-            SLA_PIN("+v"(oacc[0]), "+v"(moff), "+v"(pw[3])); SLA_SB();
-            pv(0, 1); ex(10, 11); cv2(4); fm(12, 13);
-            SLA_PIN("+v"(oacc[1]), "+v"(moff), "+v"(pw[4])); SLA_SB();
-            pv(1, 0); ex(12, 13); cv2(5); fm(14, 15); dots(0);
-            SLA_PIN("+v"(oacc[0]), "+v"(pw[5]), "+v"(l_part), "+v"(l_alt)); SLA_SB();
-            pv(1, 1); ex(14, 15); cv2(6); dots(1);
-            SLA_PIN("+v"(oacc[1]), "+v"(pw[6]), "+v"(l_part), "+v"(l_alt)); SLA_SB();
+            kf_use = load_kfrag(ck, hk);                   // (its registers are free: the four products have been issued)
+            pv(0, 0); ex(7, 8);   fm(9, 10);
+            SLA_PIN("+v"(oacc[0]), "+v"(moff)); SLA_SB();
+            pv(0, 1); cv2(3);     ex(9, 10); fm(11, 11);
+            SLA_PIN("+v"(oacc[1]), "+v"(moff), "+v"(pw[3])); SLA_SB();
+            rs(0);    cv2(4);     ex(11, 11); fm(12, 13);
+            SLA_PIN("+v"(lsum), "+v"(moff), "+v"(pw[4])); SLA_SB();
+            pv(1, 0); ex(12, 13); cv2(5); fm(14, 14);
+            SLA_PIN("+v"(oacc[0]), "+v"(moff), "+v"(pw[5])); SLA_SB();
+            pv(1, 1); fm(15, 15); ex(14, 14); cv2(6);
+            SLA_PIN("+v"(oacc[1]), "+v"(pw[6])); SLA_SB();
+            rs(1);    ex(15, 15);
+            SLA_PIN("+v"(lsum)); SLA_SB();
             cv2(7);
         } else {
             fm(0, 4);                                                            // the e4m3 MFMA takes twice as long: a larger first share
             sm(0);    ex(0, 4);   fm(5, 7);
             SLA_PIN("+v"(s_nxt), "+v"(moff)); SLA_SB();
-            pv(0, 0); ex(5, 7);   cv2(0); cv2(1); fm(8, 10);
+            kf_use = load_kfrag(ck, hk);
+            pv(0, 0); ex(5, 6);   cv2(0); cv2(1); fm(8, 8);
             SLA_PIN("+v"(oacc[0]), "+v"(moff), "+v"(pw[0]), "+v"(pw[1])); SLA_SB();
-            pv(0, 1); ex(8, 10);  cv2(2); cv2(3); fm(11, 13);
-            SLA_PIN("+v"(oacc[1]), "+v"(moff), "+v"(pw[2]), "+v"(pw[3])); SLA_SB();
-            pv(1, 0); ex(11, 13); cv2(4); fm(14, 15); dots(0);
-            SLA_PIN("+v"(oacc[0]), "+v"(pw[4]), "+v"(l_part), "+v"(l_alt)); SLA_SB();
-            pv(1, 1); ex(14, 15); cv2(5); cv2(6); dots(1);
-            SLA_PIN("+v"(oacc[1]), "+v"(pw[5]), "+v"(pw[6]), "+v"(l_part), "+v"(l_alt)); SLA_SB();
+            pv(0, 1); ex(7, 7);   cv2(2); ex(8, 8); fm(9, 10);
+            SLA_PIN("+v"(oacc[1]), "+v"(moff), "+v"(pw[2])); SLA_SB();
+            rs(0);    cv2(3);     ex(9, 9); fm(11, 11);
+            SLA_PIN("+v"(lsum), "+v"(moff), "+v"(pw[3])); SLA_SB();
+            pv(1, 0); ex(10, 11); cv2(4); fm(12, 13);
+            SLA_PIN("+v"(oacc[0]), "+v"(moff), "+v"(pw[4])); SLA_SB();
+            pv(1, 1); ex(12, 13); cv2(5); fm(14, 15);
+            SLA_PIN("+v"(oacc[1]), "+v"(pw[5])); SLA_SB();
+            rs(1);    ex(14, 14); cv2(6); ex(15, 15);
+            SLA_PIN("+v"(lsum), "+v"(pw[6])); SLA_SB();
             cv2(7);
         }
         w.p[0] = __builtin_bit_cast(f16x8, make_uint4(pw[0], pw[1], pw[2], pw[3]));
         w.p[1] = __builtin_bit_cast(f16x8, make_uint4(pw[4], pw[5], pw[6], pw[7]));
-        w.invr = t.invr;
-        over_cur = overflows(s_nxt, tn);
+        w.inv2 = t.inv2;
+        if (checked) over_cur = overflows(s_nxt, tn);
         // the fragments requested at the top of this step have long arrived: say so here, so that the wait the
         // compiler places in front of their first use in the next step does not also cover that step's own reads
         __builtin_amdgcn_s_waitcnt(0xC07F);        // lgkmcnt(0) only
-        s_cur = s_nxt; w_prev = w; vf_use = vf_pre; kf_use = kf_pre;
+        s_cur = s_nxt; w_prev = w; vf_use = vf_pre;
     };
 #undef SLA_PIN
 
-    // Raises the running maximum of the rows to the exact maximum over the unit whose S^T is s_cur, in front of a fast
-    // step: the accumulators, the row sums and the weights of the previous unit (not yet multiplied into the
-    // accumulators) are rescaled; the fast step that follows then sees no exponent above zero.
-    auto raise_reference = [&](const TileInfo &t) __attribute__((always_inline)) {
-        const float top = pair_max(max16(s_cur)) * t.cj + t.lsv;
-        const float m_new = fmaxf(m_run, top);
+    // Sets the reference exponent of the rows to m_new (never below the present one) between two steps: the accumulators,
+    // the row sums and the weights of the previous unit (not yet multiplied into the accumulators) are rescaled.
+    auto raise_to = [&](float m_new) __attribute__((always_inline)) {
         const float alpha = m_new == m_run ? 1.0f : fast_exp2(m_run - m_new);
         rescale(alpha);
         const _Float16 ah = (_Float16)alpha;
@@ -649,96 +721,132 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
             for (int x = 0; x < 8; ++x) w_prev.p[ss][x] *= ah;
         m_run = m_new;
     };
+    // In front of a fast step on a unit that would overflow: to the exact maximum over the unit whose S^T is s_cur; the
+    // fast step that follows then sees no exponent above zero.
+    auto raise_reference = [&](const TileInfo &t) __attribute__((always_inline)) { raise_to(fmaxf(m_run, pair_max(max16(s_cur)) * t.cj + t.lsv)); };
+    // Whether the exponents of all the wave's rows are bounded so tightly by |q| max |k| that no unit of the window needs
+    // the overflow check: the reference is then raised once, to where the bound makes the largest possible weight 2^kTopW
+    // (fp16 holds 2^15.99).  Not if that is more than kDrop above the exact maximum seen so far: a weight of the largest
+    // exponent seen would then be below 2^-kDrop, and fp16 keeps its full precision down to 2^-14 only.  With
+    // kDrop = 6 weights 2^-8 of the largest and more still have all their bits, smaller ones an error of 2^-19 of the largest.
+    // The check is 11 of the 62 vector instructions of a unit, and it ends every step with a vote on the last MFMA's result.
+    auto bounded_rows = [&]() __attribute__((always_inline)) {
+        const float m_need = fmaf(qnorm, w_kc, w_lv) - kTopW;
+        if (__ballot(!(m_need <= m_run + kDrop)) != 0) return false;
+        if (__ballot(m_need > m_run) != 0) raise_to(fmaxf(m_run, m_need));
+        return true;
+    };
 
-    // Ring bookkeeping.  During iteration c the LDS reads touch V^T tile c and K tile c + KAHEAD - 2 (the fragments of
-    // the following step); both must have landed at its barrier, and that barrier frees the slots of the tiles before
-    // them, into which the copies of V^T tile c + 2 and K tile c + KAHEAD go: needed two iterations later.
-    constexpr int KAHEAD = 3;
-    // Ring slots of iteration c, with P = c mod SLOTS: the V^T tile whose fragments are read sits in slot P, the K tile
-    // whose fragments are read (tile c+1) in slot P+1, the K tile requested (c+3) goes where tile c was, the V^T tile
-    // requested (c+2) into slot P+2.  The loop is unrolled over P so that the slots are constants: the fragment reads
-    // take them as immediate offsets and no slot arithmetic is left in the loop.
-    auto iteration = [&](int c, auto phase) __attribute__((always_inline)) {
-        constexpr int P = decltype(phase)::value, S = T::SLOTS;
-        constexpr uint32_t kreq = ((P + KAHEAD) % S) * T::KBYTES, vreq = ((P + 2) % S) * T::VBYTES;
-        constexpr int kslot = ((P + KAHEAD - 2) % S) * T::KBYTES, vslot = T::VRING + P * T::VBYTES;
+    // Ring bookkeeping.  During iteration c the LDS reads touch V^T tile c and K tile c+1 (the fragments of the following
+    // steps); both must have landed at its barrier, and that barrier frees the slots of the tiles before them, into which
+    // the copies of V^T tile c + SL - 1 and K tile c + SL go: needed SL - 1 iterations later.
+    constexpr int KAHEAD = SL, VAHEAD = SL - 1;
+    // Ring slots of iteration c, with P = c mod SL: the V^T tile whose fragments are read sits in slot P, the K tile
+    // whose fragments are read (tile c+1) in slot P+1, the K tile requested (c+SL) goes where tile c was, the V^T tile
+    // requested (c+SL-1) into slot P-1.
+    // The guarded form (first and last tiles of a list, ragged or far-off tiles); its slots are run-time values.
+    auto iteration = [&](int c, int P) __attribute__((always_inline)) {
+        const int P1 = P == SL - 1 ? 0 : P + 1, P2 = P == 0 ? SL - 1 : P - 1;
+        const uint32_t kreq = P * T::KBYTES, vreq = P2 * T::VBYTES;
+        const int kslot = P1 * T::KBYTES, vslot = T::VRING + P * T::VBYTES;
         SLA_T(c, 0);
         // copies that may stay in flight here: those requested one iteration ago
         if (c == 0) wait_copies_and_barrier<0>();      // (nothing is in flight; joins the waves after the prologue's LDS reads)
-        else if (c + KAHEAD - 1 < k) wait_copies_and_barrier<T::LOADS>();
-        else if (c + 1 < k) wait_copies_and_barrier<T::VINS>();
+        else if (SL > 2 && c + KAHEAD - 1 < k) wait_copies_and_barrier<T::LOADS>();
+        else if (SL > 2 && c + 1 < k) wait_copies_and_barrier<T::VINS>();
         else wait_copies_and_barrier<0>();
         SLA_T(c, 1);
         if (c + KAHEAD - wbase >= 64) load_window(wbase + 32);     // (never for lists of at most 64 blocks)
         if (c + KAHEAD < k) request_K(c + KAHEAD, kreq);
-        if (c + 2 < k) request_V(c + 2, vreq);
+        if (c + VAHEAD < k) request_V(c + VAHEAD, vreq);
         if (c + 1 == k) request_epilogue();
         const bool more = c + 1 < k;
         if (more) t_nxt = tile_info(c + 1);
-        const bool ragged_n = more && t_nxt.valid != kBK;
         SLA_T(c, 2);
         // first half of tile c: accumulates the second half of tile c-1, forms S^T of the second half of tile c;
         // reads the fragments of the next step: V^T tile c first half, K tile c+1 first half
         if (over_cur || c == 0 || t_cur.tiny || t_cur.valid != kBK) careful_step(c > 0, true, t_cur, t_cur, 1, vslot, 0, kslot, 0);
-        else fast_step(t_cur, t_cur, vslot, 0, kslot, 0);
+        else {
+            set_ones(w_prev.inv2);
+            fast_step(true, t_cur, t_cur, vslot, 0, kslot, 0);
+        }
         SLA_T(c, 3);
         // second half of tile c: accumulates its first half, forms S^T of the first half of tile c+1;
         // reads V^T tile c second half and K tile c+1 second half for the first step of the next iteration
-        if (over_cur || !more || t_cur.tiny || ragged_n) careful_step(true, more, t_cur, t_nxt, 0, vslot, 1, kslot, 1);
-        else fast_step(t_cur, t_nxt, vslot, 1, kslot, 1);
+        if (over_cur || !more || t_cur.tiny || t_nxt.valid != kBK) careful_step(true, more, t_cur, t_nxt, 0, vslot, 1, kslot, 1);
+        else {
+            set_ones(w_prev.inv2);
+            fast_step(true, t_cur, t_nxt, vslot, 1, kslot, 1);
+        }
         SLA_T(c, 4);
         t_cur = t_nxt;
     };
-    // The lean form of an iteration, for the middle of a list: tile c is not the first, tiles c .. c + KAHEAD exist, are
-    // full and none has a far-off V scale, and the window holds them (lean_ok checks this for three iterations at a
-    // time).  Nothing is conditional but the raise of the running maximum; both steps are fast steps.
-    auto lean_iteration = [&](int c, auto phase) __attribute__((always_inline)) {
-        constexpr int P = decltype(phase)::value, S = T::SLOTS;
-        constexpr uint32_t kreq = ((P + KAHEAD) % S) * T::KBYTES, vreq = ((P + 2) % S) * T::VBYTES;
-        constexpr int kslot = ((P + KAHEAD - 2) % S) * T::KBYTES, vslot = T::VRING + P * T::VBYTES;
+    // The lean form, for the middle of a list: tile c is not the first, tiles c and c+1 are full, neither has a far-off V
+    // scale, and the window holds them.  Nothing is conditional but (checked) the raise of the running maximum; both steps
+    // are fast steps.  Requests past the end of the list repeat its last tile into slots nobody reads any more, so that the
+    // number of copies in flight stays the same to the end; the last tile's guarded iteration waits for them.
+    auto lean_iteration = [&](bool checked, int c, auto phase) __attribute__((always_inline)) {
+        constexpr int P = decltype(phase)::value;
+        constexpr uint32_t kreq = P * T::KBYTES, vreq = ((P + SL - 1) % SL) * T::VBYTES;
+        constexpr int kslot = ((P + 1) % SL) * T::KBYTES, vslot = T::VRING + P * T::VBYTES;
         SLA_T(c, 0);
-        wait_copies_and_barrier<T::LOADS>();
+        wait_copies_and_barrier<SL == 2 ? 0 : T::LOADS>();
         SLA_T(c, 1);
-        request_K(c + KAHEAD, kreq, true);
-        request_V(c + 2, vreq);
+        request_K(min(c + KAHEAD, k - 1), kreq);
+        request_V(min(c + VAHEAD, k - 1), vreq);
         t_nxt.valid = kBK; t_nxt.tiny = false;
         t_nxt.cj = FP8 ? __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(d_cj), c + 1 - wbase)) : c_exp;
         t_nxt.lsv = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(d_lv), c + 1 - wbase));
-        t_nxt.invr = fast_exp2(-t_nxt.lsv);
+        t_nxt.inv2 = inv2_of(t_nxt.lsv);
         SLA_T(c, 2);
         if (over_cur) raise_reference(t_cur);
-        fast_step(t_cur, t_cur, vslot, 0, kslot, 0);
+        fast_step(checked, t_cur, t_cur, vslot, 0, kslot, 0);
         SLA_T(c, 3);
         if (over_cur) raise_reference(t_cur);
-        fast_step(t_cur, t_nxt, vslot, 1, kslot, 1);
+        set_ones(t_cur.inv2);                          // the units accumulated from here on are this tile's
+        fast_step(checked, t_cur, t_nxt, vslot, 1, kslot, 1);
         SLA_T(c, 4);
         t_cur = t_nxt;
     };
-    // three lean iterations from tile c on are possible: bits c .. c + 2 + KAHEAD of d_bad are clear and inside the window
-    auto lean_ok = [&](int c) {
-        return c + 2 + KAHEAD - wbase < 64 && ((uint32_t)(d_bad >> (c - wbase)) & ((1u << (KAHEAD + 3)) - 1)) == 0;
+    // First tile from c on that a lean iteration must not be given: the one whose successor is special, past the end of
+    // the list or past the window's end (the requests, SL tiles ahead, have to find their entries in it).
+    auto lean_end = [&](int c) {
+        const unsigned long long bad = d_bad >> (c - wbase);
+        const int run = bad ? __builtin_ctzll(bad) : 64 - (c - wbase);      // tiles c .. c + run - 1 are plain
+        const int e = c + run - 1;
+        return k - wbase > 64 ? min(e, wbase + 64 - KAHEAD) : e;
     };
-    for (int c = 0; c < k;) {
-        iteration(c, std::integral_constant<int, 0>{});
-        if (c + 1 < k) iteration(c + 1, std::integral_constant<int, 1>{});
-        if (T::SLOTS == 3 && c + 2 < k) iteration(c + 2, std::integral_constant<int, 2 % T::SLOTS>{});
-        c += T::SLOTS;
-        if constexpr (T::SLOTS == 3) {
-            while (lean_ok(c)) {
-                lean_iteration(c, std::integral_constant<int, 0>{});
-                lean_iteration(c + 1, std::integral_constant<int, 1>{});
-                lean_iteration(c + 2, std::integral_constant<int, 2>{});
-                c += 3;
+    // The lean loop, unrolled over the ring phase so that slots are constants; entered at phase 1, left at phase 1.
+    auto lean_loop = [&](bool checked, int &c, int end) __attribute__((always_inline)) {
+        do {
+            lean_iteration(checked, c, std::integral_constant<int, 1>{});
+            if constexpr (SL == 3) lean_iteration(checked, c + 1, std::integral_constant<int, 2>{});
+            lean_iteration(checked, c + SL - 1, std::integral_constant<int, 0>{});
+            c += SL;
+        } while (c + SL <= end);
+    };
+    for (int c = 0, P = 0; c < k;) {
+        iteration(c, P);
+        ++c;
+        P = P == SL - 1 ? 0 : P + 1;
+        if (P == 1 && c + KAHEAD <= k) {       // (the guarded iteration before made a full set of requests)
+            const int end = lean_end(c);
+            if (c + SL <= end) {
+                const bool checked = !bounded_rows();
+                if (!checked) over_cur = false;          // the bound covers the window, and with it the next unit
+                set_ones(w_prev.inv2);
+                lean_loop(checked, c, end);
             }
         }
     }
 #undef SLA_SB
 
     wait_copies_and_barrier<0>();                      // epilogue operands landed; every wave is past its last tile
+    const int elane = lane_now(), e32 = elane & 31, eg = elane >> 5;     // (the loop carries no lane index)
+    const int qe = i * BQ + 32 * wave_u + e32;
     SLA_TP(61, 0);
     if (k > 0) accumulate(vf_use, w_prev);             // the last unit's weights
-    l_part += l_alt;
-    float l_run = l_part + xchg32(l_part) + l_full;
+    const float l_run = lsum[0] + l_full;
 
     uint8_t *stA = lds + kHqOff, *stB = lds + kWtOff;
     const uint8_t *zrow = lds + T::ZOFF;
@@ -756,11 +864,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
         bf16x8 hfr[4][2], wfr[4][2];
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            const int hchunk = FP8 ? 4 * g + s : 2 * s + g;      // 16-byte chunk holding channels dcol(s)..dcol(s)+7
+            const int hchunk = FP8 ? 4 * eg + s : 2 * s + eg;      // 16-byte chunk holding channels dcol(s)..dcol(s)+7
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
-                hfr[s][e] = *(const bf16x8 *)(stA + (32 * e + l32) * 128 + ((hchunk ^ swz8(l32)) << 4));
-                wfr[s][e] = *(const bf16x8 *)(stB + (32 * e + l32) * 128 + (((2 * s + g) ^ swz8(l32)) << 4));
+                hfr[s][e] = *(const bf16x8 *)(stA + (32 * e + e32) * 128 + ((hchunk ^ swz8(e32)) << 4));
+                wfr[s][e] = *(const bf16x8 *)(stB + (32 * e + e32) * 128 + (((2 * s + eg) ^ swz8(e32)) << 4));
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -803,7 +911,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
         float den = 0.f;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            const int dcol = FP8 ? 32 * g + 8 * s : 16 * s + 8 * g;
+            const int dcol = FP8 ? 32 * eg + 8 * s : 16 * s + 8 * eg;
             uint4 o;
             o.x = pack_bf16(x[8 * s + 0] * inv, x[8 * s + 1] * inv); o.y = pack_bf16(x[8 * s + 2] * inv, x[8 * s + 3] * inv);
             o.z = pack_bf16(x[8 * s + 4] * inv, x[8 * s + 5] * inv); o.w = pack_bf16(x[8 * s + 6] * inv, x[8 * s + 7] * inv);
@@ -844,17 +952,17 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     SLA_TP(61, 4);
     if (O32 != nullptr) {
         // diagnostic output: the fp32 values the bf16 store below would round, straight from the accumulators
-        if (qok) {
+        if (qe < N) {
 #pragma unroll
             for (int e = 0; e < 2; ++e)
 #pragma unroll
                 for (int aa = 0; aa < 4; ++aa)
-                    *(float4 *)(O32 + head + (size_t)q * rm.ts + 32 * e + 8 * aa + 4 * g) =
+                    *(float4 *)(O32 + head + (size_t)qe * rm.ts + 32 * e + 8 * aa + 4 * eg) =
                         make_float4(oacc[e][4 * aa + 0], oacc[e][4 * aa + 1], oacc[e][4 * aa + 2], oacc[e][4 * aa + 3]);
         }
     } else {
-        uint8_t *ot = lds + T::VRING + wq * 4096;
-        const int f = ((l32 >> 1) & 7) << 1;
+        uint8_t *ot = lds + T::VRING + wave_u * 4096;
+        const int f = ((e32 >> 1) & 7) << 1;
 #pragma unroll
         for (int e = 0; e < 2; ++e)
 #pragma unroll
@@ -862,14 +970,14 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
                 uint2 o;
                 o.x = pack_bf16(oacc[e][4 * aa + 0], oacc[e][4 * aa + 1]);
                 o.y = pack_bf16(oacc[e][4 * aa + 2], oacc[e][4 * aa + 3]);
-                const int piece = 8 * e + 2 * aa + g;
-                *(uint2 *)(ot + l32 * 128 + ((piece ^ f) << 3)) = o;
+                const int piece = 8 * e + 2 * aa + eg;
+                *(uint2 *)(ot + e32 * 128 + ((piece ^ f) << 3)) = o;
             }
         wave_lds_sync();
-        const int q0w = i * BQ + 32 * wq;
+        const int q0w = i * BQ + 32 * wave_u;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-            const int r = 8 * kk + (lane >> 3), ch = lane & 7;      // row of the tile, 16-byte chunk of the row
+            const int r = 8 * kk + (elane >> 3), ch = elane & 7;      // row of the tile, 16-byte chunk of the row
             const int fr = ((r >> 1) & 7) << 1;
             const uint4 v = *(const uint4 *)(ot + r * 128 + (((2 * ch) ^ fr) << 3));
             if (q0w + r < N) *(uint4 *)(O + head + (size_t)(q0w + r) * rm.ts + ch * 8) = v;
@@ -898,18 +1006,17 @@ constexpr int kShortList = 2;
 // workgroup then lives 20 us instead of 31, but only four fit a CU instead of eight, and the launch takes the same time.)
 template <int NW, bool FP8>
 __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
-    const void *__restrict__ Qp, const void *__restrict__ Kp, const uint16_t *__restrict__ Vp, const float *__restrict__ lvs,
+    const void *__restrict__ Qp, const void *__restrict__ Kp, const uint16_t *__restrict__ Vp, const float2 *__restrict__ vks,
     const float *__restrict__ sQ, const float *__restrict__ sK, RowMap rm,
     const int32_t *__restrict__ crit_idx, int k_c, const uint16_t *__restrict__ Hq, const uint16_t *__restrict__ WT,
     int proj_per_head, int phi, int H, int N, int Nqb, int Nkb, long total, float c_exp, uint16_t *__restrict__ O, float *__restrict__ O32)
 {
-    using T = Tile<NW, FP8, 2>;                       // (for the copy-instruction counts and tile sizes only)
     constexpr int BQ = 32 * NW;
     constexpr int ES = FP8 ? 1 : 2;
     constexpr int KROWB = FP8 ? 64 : 128;
     constexpr int kA = 0, kB = 8192, kZ = 16384;      // LDS: slot A (K tile / Hq^T), slot B (V^T tile / W^T), the Z row
     __shared__ __attribute__((aligned(1024))) uint8_t lds[kZ + 256];
-    asm volatile("" ::"s"(Qp), "s"(Kp), "s"(Vp), "s"(lvs), "s"(sQ), "s"(sK), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(crit_idx),
+    asm volatile("" ::"s"(Qp), "s"(Kp), "s"(Vp), "s"(vks), "s"(sQ), "s"(sK), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(crit_idx),
                  "s"(k_c), "s"(Hq), "s"(WT), "s"(proj_per_head), "s"(phi), "s"(H), "s"(N), "s"(Nqb), "s"(Nkb), "s"(total), "s"(c_exp), "s"(O), "s"(O32));
     const long work = xcd_remap(blockIdx.x, total);
     if (work >= total) return;
@@ -949,8 +1056,7 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
     const float qscale = FP8 ? sQ[work] : 1.0f;
 
     CopyOffsets<NW, FP8> co;
-    co.init(wave, lane, krowb);
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+    co.init(__builtin_amdgcn_readfirstlane(wave), lane, krowb);
     const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_void_p)lds;
     const uint32_t ktile_bytes = (uint32_t)kBK * (uint32_t)krowb;
     const int tail_rows = N & (kBK - 1), ragged_j = tail_rows ? Nkb - 1 : -1;
@@ -959,10 +1065,8 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
     if (Hq != nullptr) {
         const uint8_t *Hi8 = (const uint8_t *)(Hq + (size_t)work * kStateElems);
         const uint8_t *Wh8 = (const uint8_t *)(WT + (proj_per_head ? (size_t)((unsigned)bh % (unsigned)H) * kD * kD : 0));
-#pragma unroll
-        for (int x = 0; x < T::VINS; ++x) copy_1k_to_lds(Hi8, co.v[x], lds_base + kA + (wave_u * T::VINS + x) * 1024);
-#pragma unroll
-        for (int x = 0; x < T::VINS; ++x) copy_1k_to_lds(Wh8, co.v[x], lds_base + kB + (wave_u * T::VINS + x) * 1024);
+        co.copy_v(Hi8, lds_base + kA);
+        co.copy_v(Wh8, lds_base + kB);
         if (tid < 8) copy_1k_to_lds(Hi8 + 64 * kD * 2, tid * 16, lds_base + kZ);
     }
     // number of leading valid entries, their V exponents and exp2 constants (a gather that depends on the list)
@@ -971,7 +1075,7 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
     int k = okm == ~0ull ? 64 : __builtin_ctzll(~okm);
     k = __builtin_amdgcn_readfirstlane(min(k, k_c));
     const int d_j = jok ? j0 : 0;
-    float d_lv = lvs[bh * Nkb + d_j];
+    float d_lv = vks[bh * Nkb + d_j].x;
     float d_cj = FP8 ? fmaxf(c_exp * qscale * sK[bh * Nkb + d_j], 1e-30f) : c_exp;
     asm volatile("" : "+v"(d_lv), "+v"(d_cj));
     const float lv_ref = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(d_lv)));
@@ -1067,14 +1171,9 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
     auto request_tile = [&](int c) __attribute__((always_inline)) {
         const uint32_t j = (uint32_t)__builtin_amdgcn_readlane(d_j, c);
         const uint8_t *kt = Kh + (uint64_t)j * ktile_bytes;
-        const uint32_t kdst = lds_base + kA + wave_u * T::KINS * 1024, vdst = lds_base + kB + wave_u * T::VINS * 1024;
-        if ((int)j != ragged_j) copy_nk_to_lds<T::KINS>(kt, co.k, kdst);
-        else {
-#pragma unroll
-            for (int x = 0; x < T::KINS; ++x)
-                copy_1k_to_lds(kt, co.k[x] - (co.krow[x] - min(co.krow[x], tail_rows - 1)) * krowb, kdst + x * 1024);
-        }
-        copy_nk_to_lds<T::VINS>(Vh + (uint64_t)j * (uint32_t)(kBK * kD * 2), co.v, vdst);
+        if ((int)j != ragged_j) co.copy_k(kt, lds_base + kA);
+        else co.copy_k_ragged(kt, lds_base + kA, tail_rows, krowb);
+        co.copy_v(Vh + (uint64_t)j * (uint32_t)(kBK * kD * 2), lds_base + kB);
     };
 
     // ---- the tiles, one at a time
@@ -1209,17 +1308,17 @@ hipError_t launch_transpose_w(const void *W, int nW, void *WT, hipStream_t st)
 }
 
 template <int NW, bool FP8, int SL = 3>
-static hipError_t launch_attend_t(const void *Q, const void *K, const void *Vp, const float *lvs, const float *sQ, const float *sK, RowMap rm,
+static hipError_t launch_attend_t(const void *Q, const void *K, const void *Vp, const float2 *vks, const float *sQ, const float *sK, RowMap rm,
                                   const int32_t *crit_idx, int k_c, const void *Hq, const void *WT, int proj_per_head, int phi,
                                   int H, int N, int Nqb, int Nkb, long total, float c_exp, void *O, float *O32, hipStream_t st)
 {
-    attend_kernel<NW, FP8, SL><<<(unsigned)xcd_grid(total), 64 * NW, 0, st>>>(Q, K, (const uint16_t *)Vp, lvs, sQ, sK, rm, crit_idx, k_c, (const uint16_t *)Hq,
+    attend_kernel<NW, FP8, SL><<<(unsigned)xcd_grid(total), 64 * NW, 0, st>>>(Q, K, (const uint16_t *)Vp, vks, sQ, sK, rm, crit_idx, k_c, (const uint16_t *)Hq,
                                                                      (const uint16_t *)WT, proj_per_head, phi, H, N, Nqb, Nkb,
                                                                      total, c_exp, (uint16_t *)O, O32);
     return hipGetLastError();
 }
 
-hipError_t launch_attend(const void *Q, const void *K, const void *Vp, const float *lvs,
+hipError_t launch_attend(const void *Q, const void *K, const void *Vp, const float2 *vks,
                          const float *sQ, const float *sK, bool fp8, RowMap rm,
                          const int32_t *crit_idx, int k_c, const void *Hq, const void *WT,
                          int proj_per_head, int phi, int B, int H, int N, int bq, float sm_scale,
@@ -1228,18 +1327,18 @@ hipError_t launch_attend(const void *Q, const void *K, const void *Vp, const flo
     const int Nqb = (N + bq - 1) / bq, Nkb = (N + kBK - 1) / kBK;
     const long total = (long)B * H * Nqb;
     const float c_exp = sm_scale * kLog2e;
-#define SLA_ATT(NW, F8, SL) return launch_attend_t<NW, F8, SL>(Q, K, Vp, lvs, sQ, sK, rm, crit_idx, k_c, Hq, WT, proj_per_head, phi, H, N, Nqb, Nkb, total, c_exp, O, O32, st)
+#define SLA_ATT(NW, F8, SL) return launch_attend_t<NW, F8, SL>(Q, K, Vp, vks, sQ, sK, rm, crit_idx, k_c, Hq, WT, proj_per_head, phi, H, N, Nqb, Nkb, total, c_exp, O, O32, st)
     if (bq == 128) { if (fp8) SLA_ATT(4, true, 3); else SLA_ATT(4, false, 3); }
     // lists of at most two blocks (frame attention): the kernel without a pipeline, eight workgroups per CU
     if (k_c <= kShortList) {
-        if (fp8) attend_short_kernel<2, true><<<(unsigned)xcd_grid(total), 128, 0, st>>>(Q, K, (const uint16_t *)Vp, lvs, sQ, sK, rm, crit_idx, k_c, (const uint16_t *)Hq,
+        if (fp8) attend_short_kernel<2, true><<<(unsigned)xcd_grid(total), 128, 0, st>>>(Q, K, (const uint16_t *)Vp, vks, sQ, sK, rm, crit_idx, k_c, (const uint16_t *)Hq,
                                                                                        (const uint16_t *)WT, proj_per_head, phi, H, N, Nqb, Nkb, total, c_exp, (uint16_t *)O, O32);
-        else attend_short_kernel<2, false><<<(unsigned)xcd_grid(total), 128, 0, st>>>(Q, K, (const uint16_t *)Vp, lvs, sQ, sK, rm, crit_idx, k_c, (const uint16_t *)Hq,
+        else attend_short_kernel<2, false><<<(unsigned)xcd_grid(total), 128, 0, st>>>(Q, K, (const uint16_t *)Vp, vks, sQ, sK, rm, crit_idx, k_c, (const uint16_t *)Hq,
                                                                                       (const uint16_t *)WT, proj_per_head, phi, H, N, Nqb, Nkb, total, c_exp, (uint16_t *)O, O32);
         return hipGetLastError();
     }
-    if (fp8) SLA_ATT(2, true, 3);
-    SLA_ATT(2, false, 3);
+    if (fp8) SLA_ATT(2, true, 2);
+    SLA_ATT(2, false, 2);
 #undef SLA_ATT
 }
 

@@ -13,7 +13,8 @@
 // The fp16 copy of V is exact: bf16 values are first divided by the power of two 2^e of the block's largest
 // magnitude (so that any bf16 tensor fits the range of fp16; entries more than 2^24 below the block's maximum
 // are the only ones to lose bits), E4M3 codes are taken as they are; the attention kernel gets e, or the base-2
-// logarithm of the E4M3 block scale, in `lvs` and folds it into the exponent of its softmax weights.
+// logarithm of the E4M3 block scale, in `vks` and folds it into the exponent of its softmax weights; beside it the
+// largest norm of the block's K rows (e4m3: of the codes), with which that kernel bounds its exponents.
 // The loads of the next block are in flight (in registers) while the current one is processed, and the
 // state and V^T tiles leave through LDS so that every store instruction writes 1 KB of whole rows:
 // the kernel is bound by HBM (16 KB in, 16.6 KB out per block for bf16 inputs).  A few workgroups past
@@ -176,11 +177,11 @@ template <bool FP8>
 __global__ __launch_bounds__(64 * kWavesPerWG) __attribute__((amdgpu_waves_per_eu(2, 2))) void states_kernel(const void *__restrict__ K, const void *__restrict__ V,
                                                                   const float *__restrict__ sK, const float *__restrict__ sV,
                                                                   RowMap rm, int N, int Nkb, long nblocks, int per_wave,
-                                                                  uint16_t *__restrict__ hT, uint16_t *__restrict__ Vp, float *__restrict__ lvs,
+                                                                  uint16_t *__restrict__ hT, uint16_t *__restrict__ Vp, float2 *__restrict__ vks,
                                                                   double *__restrict__ kbar, int phi, unsigned state_wgs,
                                                                   const uint16_t *__restrict__ W, uint16_t *__restrict__ WT)
 {
-    asm volatile("" ::"s"(K), "s"(V), "s"(sK), "s"(sV), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(N), "s"(Nkb), "s"(nblocks), "s"(per_wave), "s"(hT), "s"(Vp), "s"(lvs), "s"(kbar), "s"(phi), "s"(state_wgs), "s"(W), "s"(WT));      // all kernel arguments in one batch of scalar loads, here
+    asm volatile("" ::"s"(K), "s"(V), "s"(sK), "s"(sV), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(N), "s"(Nkb), "s"(nblocks), "s"(per_wave), "s"(hT), "s"(Vp), "s"(vks), "s"(kbar), "s"(phi), "s"(state_wgs), "s"(W), "s"(WT));      // all kernel arguments in one batch of scalar loads, here
     if (blockIdx.x >= state_wgs) {     // workgroups past the states grid each lay out one projection matrix for the attention kernel
         const size_t m = (size_t)(blockIdx.x - state_wgs) * kD * kD;
         transpose_w_tile(W + m, WT + m, 64 * kWavesPerWG);
@@ -237,14 +238,18 @@ __global__ __launch_bounds__(64 * kWavesPerWG) __attribute__((amdgpu_waves_per_e
 
         // ---- phi: lane t owns token row t
         float x[64];
+        float kn[4] = {0.f, 0.f, 0.f, 0.f}, knorm;   // largest norm of the block's K rows, from above (rows past a ragged end
+                                                     // repeat the last one)
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             const uint4 w = *(const uint4 *)(Ks + lane * kLdsRow + c * 8);
+            kn[c & 3] = dot2_bf16(w.x, w.x, dot2_bf16(w.y, w.y, dot2_bf16(w.z, w.z, dot2_bf16(w.w, w.w, kn[c & 3]))));
             x[c * 8 + 0] = bf16_lo(w.x); x[c * 8 + 1] = bf16_hi(w.x);
             x[c * 8 + 2] = bf16_lo(w.y); x[c * 8 + 3] = bf16_hi(w.y);
             x[c * 8 + 4] = bf16_lo(w.z); x[c * 8 + 5] = bf16_hi(w.z);
             x[c * 8 + 6] = bf16_lo(w.w); x[c * 8 + 7] = bf16_hi(w.w);
         }
+        knorm = norm_from_above(wave_max_dpp((kn[0] + kn[1]) + (kn[2] + kn[3])));
         // phi = 0: softmax over the 64 channels; phi = 1: ELU(x)+1 elementwise (x+1 above 0, exp(x) below).
         // s is 1 for bf16 inputs and the K block scale for e4m3.
         const float cexp = (FP8 ? sK[blk] : 1.0f) * 1.4426950408889634f;
@@ -283,16 +288,19 @@ __global__ __launch_bounds__(64 * kWavesPerWG) __attribute__((amdgpu_waves_per_e
                 const uint2 hi = bf16x4_to_f16x4(*(const uint2 *)(Vt + e * kLdsRow + src + 8), 127 - vexp);
                 *(uint4 *)(vt + e * kBK + 8 * c) = make_uint4(lo.x, lo.y, hi.x, hi.y);
             }
-            if (lane == 0) lvs[blk] = FP8 ? __log2f(fmaxf(sV[blk], 1e-30f)) : (float)(vexp - 127);
+            if (lane == 0) vks[blk] = make_float2(FP8 ? __log2f(fmaxf(sV[blk], 1e-30f)) : (float)(vexp - 127), knorm);
         }
 
         // ---- z: lane d sums phi^T row d (the bf16 values the product below consumes)
-        float z = 0.f;
+        constexpr uint32_t kOnes = 0x3F803F80u;                 // two bf16 1.0: a dot product with them adds a pair of values
+        float z0 = 0.f, z1 = 0.f;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             const uint4 w = *(const uint4 *)(Ks + lane * kLdsRow + c * 8);
-            z += bf16_lo(w.x) + bf16_hi(w.x) + bf16_lo(w.y) + bf16_hi(w.y) + bf16_lo(w.z) + bf16_hi(w.z) + bf16_lo(w.w) + bf16_hi(w.w);
+            z0 = dot2_bf16(w.z, kOnes, dot2_bf16(w.x, kOnes, z0));
+            z1 = dot2_bf16(w.w, kOnes, dot2_bf16(w.y, kOnes, z1));
         }
+        const float z = z0 + z1;
 
         // ---- h[d][e] = sum_t phi^T[d][t] * V^T[e][t]
         f32x16 zero16;
@@ -341,7 +349,7 @@ __global__ __launch_bounds__(64 * kWavesPerWG) __attribute__((amdgpu_waves_per_e
 }
 
 hipError_t launch_states(const void *K, const void *V, const float *sK, const float *sV, bool fp8, RowMap rm,
-                         int BH, int N, void *hT, void *Vp, float *lvs, double *kbar, int phi, const void *W, int nW, void *WT, hipStream_t st)
+                         int BH, int N, void *hT, void *Vp, float2 *vks, double *kbar, int phi, const void *W, int nW, void *WT, hipStream_t st)
 {
     const int Nkb = (N + kBK - 1) / kBK;
     const long nblocks = (long)BH * Nkb;
@@ -351,8 +359,8 @@ hipError_t launch_states(const void *K, const void *V, const float *sK, const fl
     const long waves = (nblocks + per_wave - 1) / per_wave;
     const unsigned grid = (unsigned)((waves + kWavesPerWG - 1) / kWavesPerWG);
     const unsigned extra = W != nullptr ? (unsigned)nW : 0u;
-    if (fp8) states_kernel<true><<<grid + extra, 64 * kWavesPerWG, 0, st>>>(K, V, sK, sV, rm, N, Nkb, nblocks, per_wave, (uint16_t *)hT, (uint16_t *)Vp, lvs, kbar, phi, grid, (const uint16_t *)W, (uint16_t *)WT);
-    else     states_kernel<false><<<grid + extra, 64 * kWavesPerWG, 0, st>>>(K, V, sK, sV, rm, N, Nkb, nblocks, per_wave, (uint16_t *)hT, (uint16_t *)Vp, lvs, kbar, phi, grid, (const uint16_t *)W, (uint16_t *)WT);
+    if (fp8) states_kernel<true><<<grid + extra, 64 * kWavesPerWG, 0, st>>>(K, V, sK, sV, rm, N, Nkb, nblocks, per_wave, (uint16_t *)hT, (uint16_t *)Vp, vks, kbar, phi, grid, (const uint16_t *)W, (uint16_t *)WT);
+    else     states_kernel<false><<<grid + extra, 64 * kWavesPerWG, 0, st>>>(K, V, sK, sV, rm, N, Nkb, nblocks, per_wave, (uint16_t *)hT, (uint16_t *)Vp, vks, kbar, phi, grid, (const uint16_t *)W, (uint16_t *)WT);
     return hipGetLastError();
 }
 

@@ -69,6 +69,10 @@ __device__ __forceinline__ float bf16_round(float x) { return (float)(__bf16)x; 
 // exp2 on the hardware transcendental unit (v_exp_f32); exp2(-inf) = 0
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// 2-norm from a sum of squares, rounded up past the rounding of the sum (64 terms in fp32), and with a floor where squares
+// may have underflowed: an upper bound
+__device__ __forceinline__ float norm_from_above(float ss) { return fmaf(__builtin_amdgcn_sqrtf(ss), 1.001f, 1.7347235e-18f); }
+
 // value held by the lane 32 positions away (lanes l and l^32 exchange)
 __device__ __forceinline__ float xchg32(float v) { return __shfl_xor(v, 32, 64); }
 
@@ -76,6 +80,22 @@ __device__ __forceinline__ float wave_max(float v)
 {
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
     return v;
+}
+// maximum over the wave, uniform (DPP row shifts, then the two row broadcasts; lane 63 ends with the result)
+template <int CTRL, int ROWS> __device__ __forceinline__ float dpp_max_step(float v)
+{
+    const int u = (int)__float_as_uint(v);
+    return fmaxf(v, __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(u, u, CTRL, ROWS, 0xf, false)));
+}
+__device__ __forceinline__ float wave_max_dpp(float v)
+{
+    v = dpp_max_step<0x111, 0xf>(v);
+    v = dpp_max_step<0x112, 0xf>(v);
+    v = dpp_max_step<0x114, 0xf>(v);
+    v = dpp_max_step<0x118, 0xf>(v);
+    v = dpp_max_step<0x142, 0xa>(v);
+    v = dpp_max_step<0x143, 0xc>(v);
+    return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), 63));
 }
 __device__ __forceinline__ float wave_sum(float v)
 {
