@@ -462,8 +462,8 @@ sla_status_t sla_fp8_linear(const void *x, const void *W, const void *bias, int3
     if (!aligned(workspace, 256)) return fail(SLA_ERR_WORKSPACE, "workspace must be 256-byte aligned");
     if (workspace_bytes < lp.total) return fail(SLA_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, lp.total);
     hipStream_t st = (hipStream_t)stream;
-    SLA_HIP(sla::launch_quantise_rows(x, N, d_in, at<void>(workspace, lp.off_cx), at<float>(workspace, lp.off_sx), st));
-    SLA_HIP(sla::launch_quantise_rows(W, d_out, d_in, at<void>(workspace, lp.off_cw), at<float>(workspace, lp.off_sw), st));
+    SLA_HIP(sla::launch_quantise_rows(x, N, at<void>(workspace, lp.off_cx), at<float>(workspace, lp.off_sx), W, d_out,
+                                      at<void>(workspace, lp.off_cw), at<float>(workspace, lp.off_sw), d_in, st));
     SLA_HIP(sla::launch_fp8_gemm(at<void>(workspace, lp.off_cx), at<float>(workspace, lp.off_sx), at<void>(workspace, lp.off_cw),
                                  at<float>(workspace, lp.off_sw), bias, N, d_out, d_in, y, st));
     return SLA_OK;
@@ -491,8 +491,8 @@ sla_status_t sla_fp8_linear_qkv(const void *x, const void *W, const void *bias, 
     if (!aligned(workspace, 256)) return fail(SLA_ERR_WORKSPACE, "workspace must be 256-byte aligned");
     if (workspace_bytes < lp.total) return fail(SLA_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, lp.total);
     hipStream_t st = (hipStream_t)stream;
-    SLA_HIP(sla::launch_quantise_rows(x, tokens, d_in, at<void>(workspace, lp.off_cx), at<float>(workspace, lp.off_sx), st));
-    SLA_HIP(sla::launch_quantise_rows(W, d_out, d_in, at<void>(workspace, lp.off_cw), at<float>(workspace, lp.off_sw), st));
+    SLA_HIP(sla::launch_quantise_rows(x, tokens, at<void>(workspace, lp.off_cx), at<float>(workspace, lp.off_sx), W, d_out,
+                                      at<void>(workspace, lp.off_cw), at<float>(workspace, lp.off_sw), d_in, st));
     void *const codes[3] = {Q8, K8, V8};
     float *const scales[3] = {sQ, sK, sV};
     SLA_HIP(sla::launch_fp8_gemm_qkv(at<void>(workspace, lp.off_cx), at<float>(workspace, lp.off_sx), at<void>(workspace, lp.off_cw),

@@ -120,6 +120,56 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16 &a, int base)
     return __builtin_bit_cast(bf16x8, o);
 }
 
+// x / scale for many x and one block scale = max(amax, 1e-8) / 448 of bf16 values, with the bits of the IEEE division:
+// y = RN(1 / d) once (a true division), then q = RN(x y), r = d q - x (exact in one fma), RN(q - r y) is the correctly
+// rounded quotient (Markstein's division step; written with this sign of r, a zero quotient keeps the sign of x).  It needs y correctly rounded and fails only for a significand of d of all
+// ones, which no such scale has: amax is m 2^e with m below 256, m / 7 differs from every power of two by a part in 256 or
+// is equal to it, and 1e-8 / 448 is one number (tests/test_division_step.py goes through all of them).  Quotients are at
+// most 448 in magnitude and anything below 2^-10 becomes the code 0, so the exponent range plays no part for a finite scale.
+// Three instructions per element instead of the ten of the division's expansion.
+// An infinite scale: x / inf is a zero of x's sign, and NaN for an infinite x.  d = 0 and y = 0 give just that
+// (q = x 0, RN(q + x 0)); the qkv epilogue does not ask for it (NaN for every x: the code of -448).
+struct BlockDivisor {
+    float d, y;
+    __device__ __forceinline__ explicit BlockDivisor(float scale, bool infinite = false)
+        : d(infinite && scale == __builtin_inff() ? 0.f : scale), y(1.0f / scale) {}
+    __device__ __forceinline__ float operator()(float x) const
+    {
+        const float q = x * y;
+        return fmaf(-fmaf(q, d, -x), y, q);
+    }
+};
+
+// four E4M3 codes of four clamped values (v_cvt_pk_fp8_f32 rounds to nearest even)
+__device__ __forceinline__ uint32_t pack_e4m3(float a, float b, float c, float d)
+{
+    int u = 0;
+    u = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, u, false);
+    u = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, u, true);
+    return (uint32_t)u;
+}
+
+// max(m, |a|, |b|) where neither a nor b is a signalling NaN (the compiler would quiet each operand of fmaxf first)
+__device__ __forceinline__ float max3_abs(float m, float a, float b)
+{
+    asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(m) : "v"(m), "v"(a), "v"(b));
+    return m;
+}
+
+// the codes of sixteen bf16 values
+__device__ __forceinline__ uint4 quantise16(const uint32_t (&w)[8], const BlockDivisor &divide)
+{
+    uint32_t o[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float y[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) y[r] = fminf(fmaxf(divide((r & 1) ? bf16_hi(w[2 * q + r / 2]) : bf16_lo(w[2 * q + r / 2])), -448.0f), 448.0f);
+        o[q] = pack_e4m3(y[0], y[1], y[2], y[3]);
+    }
+    return make_uint4(o[0], o[1], o[2], o[3]);
+}
+
 // Orders LDS traffic between the lanes of one wavefront (LDS operations of a wave execute in
 // program order; this only stops the compiler from moving accesses across the point).
 __device__ __forceinline__ void wave_lds_sync()

@@ -110,26 +110,28 @@ def probe_select_report(L: ctypes.CDLL, nkb: int) -> None:
 
 def probe_gemm(M: int) -> None:
     L = _use_probe_library()
-    d_in, d_out = 1024, 3072
+    d_in, d_out, H = 1024, 3072, 16
     g = torch.Generator(device="cuda").manual_seed(1)
     x = torch.randn((M, d_in), device="cuda", generator=g).to(torch.bfloat16)
     W = (torch.randn((d_out, d_in), device="cuda", generator=g) / 32).to(torch.bfloat16)
     b = torch.randn((d_out,), device="cuda", generator=g).to(torch.bfloat16)
     y = torch.empty((M, d_out), dtype=torch.bfloat16, device="cuda")
-    for _ in range(8):
-        B.sla_fp8_linear(x, W, b, y)
-    torch.cuda.synchronize()
-    buf = (ctypes.c_ulonglong * 16)()
-    if L.sla_probe_read_gemm(buf) != 0:
-        raise RuntimeError("sla_probe_read_gemm failed")
-    t = list(buf)
-    c, r = t[:8], t[8:]
-    print(f"fp8 GEMM [{M} x {d_in}] x [{d_in} x {d_out}], one wave of one workgroup:")
-    names = ["start -> first tiles landed", "main loop", "last barrier", "accumulators -> LDS (scale, bias, bf16)", "stores (issue + completion)"]
-    for i, n in enumerate(names):
-        print("  %-42s %7d cycles  %6.2f us" % (n, c[i + 1] - c[i], (r[i + 1] - r[i]) / 100.0))
-    print("  tile total %d cycles in %.2f us -> %.3f GHz" % (c[5] - c[0], (r[5] - r[0]) / 100.0, (c[5] - c[0]) / max(1, r[5] - r[0]) * 0.1))
-    print("  inside the main loop: waiting for copies %d cycles, then for the barrier %d cycles (about 100 of probe per step included)" % (c[6], c[7]))
+    codes = [torch.empty((1, M, H, 64), dtype=torch.uint8, device="cuda") for _ in range(3)]
+    scales = [torch.empty((1, H, -(-M // blk)), dtype=torch.float32, device="cuda") for blk in (128, 64, 64)]
+    for what, call in (("layer", lambda: B.sla_fp8_linear(x, W, b, y)),
+                       ("qkv projection", lambda: B.sla_fp8_linear_qkv(x, W, b, 1, M, H, 128, *codes, *scales))):
+        for _ in range(8):
+            call()
+        torch.cuda.synchronize()
+        buf = (ctypes.c_ulonglong * 16)()
+        if L.sla_probe_read_gemm(buf) != 0:
+            raise RuntimeError("sla_probe_read_gemm failed")
+        c, r = list(buf)[:8], list(buf)[8:]
+        print(f"FP8 GEMM [{M} x {d_in}] x [{d_in} x {d_out}], {what}, one wave of one workgroup:")
+        names = ["start -> first copies asked for", "main loop", "epilogue, stores asked for", "stores completed"]
+        for i, n in enumerate(names):
+            print("  %-42s %7d cycles  %6.2f us" % (n, c[i + 1] - c[i], (r[i + 1] - r[i]) / 100.0))
+        print("  tile total %d cycles in %.2f us -> %.3f GHz" % (c[4] - c[0], (r[4] - r[0]) / 100.0, (c[4] - c[0]) / max(1, r[4] - r[0]) * 0.1))
 
 
 def main() -> None:

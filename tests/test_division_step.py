@@ -52,3 +52,38 @@ def test_division_step_on_exact_ties_of_the_code_grid():
         dd = np.full(x.shape, d, dtype=np.float32)
         out.append(np.array_equal(_step(x, dd).view(np.uint32), (x / dd).astype(np.float32).view(np.uint32)))
     assert out and all(out)
+
+
+def test_no_block_scale_has_a_significand_of_all_ones():
+    """The division step needs RN(1/d) correctly rounded and a significand of d that is not all ones: every scale that a
+    bf16 maximum gives, all 32640 of them."""
+    amax = (np.arange(0x7F80, dtype=np.uint32) << np.uint32(16)).view(np.float32)
+    d = (np.maximum(amax, np.float32(1e-8)) / np.float32(448.0)).astype(np.float32)
+    assert ((d.view(np.uint32) & np.uint32(0x7FFFFF)) != np.uint32(0x7FFFFF)).all()
+
+
+def _step_signed(x, d, y):
+    """The same step with r = d q - x and RN(q - r y): a zero quotient keeps the sign of x."""
+    q = (x * y).astype(np.float32)
+    return _fma32(-_fma32(q, d, -x), y, q)
+
+
+def test_signed_step_equals_ieee_division_zeros_included():
+    rng = np.random.default_rng(6)
+    n = 500_000
+    amax = _bf16(np.exp(rng.uniform(-20, 20, n)).astype(np.float32))
+    d = (np.maximum(amax, np.float32(1e-8)) / np.float32(448.0)).astype(np.float32)
+    x = _bf16(amax * rng.uniform(-1, 1, n).astype(np.float32))
+    x[::7], x[::11] = 0.0, -0.0
+    got = _step_signed(x, d, (np.float32(1.0) / d).astype(np.float32))
+    assert np.array_equal(got.view(np.uint32), (x / d).astype(np.float32).view(np.uint32))
+
+
+def test_zero_divisor_and_reciprocal_stand_for_an_infinite_scale():
+    x = _bf16(np.array([0.0, -0.0, 1.0, -3.0, 3e38, -1e-30, np.inf, -np.inf], dtype=np.float32))
+    with np.errstate(invalid="ignore"):
+        want = x / np.float32(np.inf)
+        got = _step_signed(x, np.zeros_like(x), np.zeros_like(x))
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    ok = ~np.isnan(want)
+    assert np.array_equal(got[ok].view(np.uint32), want[ok].view(np.uint32))
