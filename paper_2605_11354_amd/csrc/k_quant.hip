@@ -25,34 +25,30 @@ __global__ __launch_bounds__(256) void quantise_e4m3_kernel(const uint16_t *__re
     uint32_t w[kPieces][4];
     float amax = 0.f;
 #pragma unroll
-    for (int k = 0; k < kPieces; ++k) {
-        const int r = (lane >> 3) + 8 * k;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (r < valid) v = *(const uint4 *)(x + (size_t)r * rm.ts);
+    for (int k = 0; k < kPieces; ++k) {              // rows past the end repeat the last one: no predicate, and the maximum is the same
+        const int r = min((lane >> 3) + 8 * k, valid - 1);
+        const uint4 v = *(const uint4 *)(x + (size_t)r * rm.ts);
         w[k][0] = v.x; w[k][1] = v.y; w[k][2] = v.z; w[k][3] = v.w;
+    }
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k)
 #pragma unroll
         for (int c = 0; c < 4; ++c) amax = fmaxf(amax, fmaxf(fabsf(bf16_lo(w[k][c])), fabsf(bf16_hi(w[k][c]))));
-    }
-    amax = wave_max(amax);
+    amax = wave_max_dpp(amax);
     const float scale = fmaxf(amax, 1e-8f) / 448.0f;
     if (lane == 0) scales[blk] = scale;
     uint8_t *out = codes + rm.head(bh) + (size_t)t0 * rm.ts + (lane & 7) * 8;
+    const BlockDivisor divide(scale, true);
 #pragma unroll
     for (int k = 0; k < kPieces; ++k) {
         const int r = (lane >> 3) + 8 * k;
-        if (r >= valid) continue;
         float y[8];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            y[2 * c] = fminf(fmaxf(bf16_lo(w[k][c]) / scale, -448.0f), 448.0f);
-            y[2 * c + 1] = fminf(fmaxf(bf16_hi(w[k][c]) / scale, -448.0f), 448.0f);
+            y[2 * c] = fminf(fmaxf(divide(bf16_lo(w[k][c])), -448.0f), 448.0f);
+            y[2 * c + 1] = fminf(fmaxf(divide(bf16_hi(w[k][c])), -448.0f), 448.0f);
         }
-        int lo = 0, hi = 0;
-        lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], lo, false);
-        lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], lo, true);
-        hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[4], y[5], hi, false);
-        hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[6], y[7], hi, true);
-        *(uint2 *)(out + (size_t)r * rm.ts) = make_uint2((uint32_t)lo, (uint32_t)hi);
+        if (r < valid) *(uint2 *)(out + (size_t)r * rm.ts) = make_uint2(pack_e4m3(y[0], y[1], y[2], y[3]), pack_e4m3(y[4], y[5], y[6], y[7]));
     }
 }
 
