@@ -32,81 +32,60 @@ struct RowsIn {
     float *scales;
 };
 
-// A workgroup takes one group of 32 rows: lane 4 r + c of wave w reads channels 64 s + 16 c .. + 15 of rows r and r + 16
-// for the slices s = w, w + 4, ... (a quad reads one 128-byte line), holds them in registers through the maximum over the
-// row (quad, then the four waves through LDS) and writes a piece of sixteen codes per slice and row: runs of 256 bytes.
-// HBM bound (2 bytes in, 1 out per element) once the division is BlockDivisor's three instructions: with the division's
-// own expansion the vector unit took as long as the memory.  Rows longer than 256 SL channels are read twice.
-// The first groups belong to matrix a, the others to b: the few rows of the weights would be a launch of their own, most of
-// which is waiting.  Measured: 43968 + 3072 rows of 1024 in 29 us = 4.8 TB/s (two launches, a row per wave read twice, with
-// the division's expansion: 32 + 5.3 us); 1374 + 3072 rows 10 us (4.3 + 7.3 us and the gap between them).
-template <int SL, int HALVES>                        // slices per wave and pass; halves of a group per workgroup
+// A workgroup takes half a group, 16 rows: lane 4 r + c of wave w reads channels 64 s + 16 c .. + 15 of row r for the slices
+// s = w, w + 4, ... (a quad reads one 128-byte line), holds them in registers through the maximum over the row (quad, then
+// the four waves through LDS) and writes a piece of sixteen codes per slice: runs of 256 bytes.  Rows of more than 256 SL
+// channels are read twice (ONE = false).  HBM bound (2 bytes in, 1 out per element) once the division is BlockDivisor's
+// three instructions: with the division's own expansion the vector unit took as long as the memory.
+// The first half groups belong to matrix a, the others to b: the few rows of the weights would be a launch of their own,
+// most of which is waiting.  Measured: 43968 + 3072 rows of 1024 in 25 us = 5.5 TB/s (two launches, a row per wave read twice, with
+// the division's expansion: 32 + 5.3 us); 1374 + 3072 rows 8.6 us (4.3 + 7.3 us and the gap between them).
+template <int SL, bool ONE>                          // slices per wave and pass; rows of one pass
 __global__ __launch_bounds__(256) void quantise_rows_kernel(RowsIn ma, RowsIn mb, int cols)
 {
     asm volatile("" ::"s"(ma.X), "s"(ma.rows), "s"(ma.codes), "s"(ma.scales), "s"(mb.X), "s"(mb.rows), "s"(mb.codes), "s"(mb.scales), "s"(cols));      // all kernel arguments in one batch of scalar loads, here
-    __shared__ float red[4][32];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 3;
-    const long groups_a = (ma.rows + 31) / 32;
-    const long blk = HALVES == 2 ? (long)blockIdx.x : (long)(blockIdx.x >> 1);
-    const int h0 = HALVES == 2 ? 0 : 16 * (int)(blockIdx.x & 1);                  // first row of the workgroup within the group
+    __shared__ float red[4][16];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 3, r0 = lane >> 2;
+    const long groups_a = (ma.rows + 31) / 32, blk = blockIdx.x >> 1;
     const bool first = blk < groups_a;
-    const int r0 = h0 + (lane >> 2);
     const RowsIn m = first ? ma : mb;
     const long grp = first ? blk : blk - groups_a;
-    const int R = (int)min(32L, m.rows - 32 * grp);                              // rows of this group, >= 1
-    const uint16_t *x = m.X + 32 * grp * cols + 16 * c;
-    const int slices = cols / kSlice, passes = (slices + 4 * SL - 1) / (4 * SL);
-    uint32_t w[SL][HALVES][8];
+    const int R = (int)min(32L, m.rows - 32 * grp), row = 16 * (int)(blockIdx.x & 1) + r0;    // rows of the group (>= 1), this lane's
+    const uint16_t *const x = m.X + (32 * grp + min(row, R - 1)) * cols + 16 * c;    // rows past the end repeat the last one
+    const int slices = cols / kSlice, passes = ONE ? 1 : (slices + 4 * SL - 1) / (4 * SL);
+    uint32_t w[SL][8];
     auto load = [&](int p) {
 #pragma unroll
-        for (int k = 0; k < SL; ++k)
-#pragma unroll
-            for (int half = 0; half < HALVES; ++half) {
-                const int s = (p * SL + k) * 4 + wave, r = r0 + 16 * half;
-                uint4 u = make_uint4(0u, 0u, 0u, 0u), v = u;
-                if (s < slices && r < R) {
-                    u = *(const uint4 *)(x + (long)r * cols + s * kSlice);
-                    v = *(const uint4 *)(x + (long)r * cols + s * kSlice + 8);
-                }
-                w[k][half][0] = u.x; w[k][half][1] = u.y; w[k][half][2] = u.z; w[k][half][3] = u.w;
-                w[k][half][4] = v.x; w[k][half][5] = v.y; w[k][half][6] = v.z; w[k][half][7] = v.w;
-            }
+        for (int k = 0; k < SL; ++k) {               // and slices: no predicate, and the maximum is the same
+            const uint16_t *const at = x + min((p * SL + k) * 4 + wave, slices - 1) * kSlice;
+            const uint4 u = *(const uint4 *)at, v = *(const uint4 *)(at + 8);
+            w[k][0] = u.x; w[k][1] = u.y; w[k][2] = u.z; w[k][3] = u.w;
+            w[k][4] = v.x; w[k][5] = v.y; w[k][6] = v.z; w[k][7] = v.w;
+        }
     };
-    float amax[HALVES] = {};
+    float amax = 0.f;
     for (int p = 0; p < passes; ++p) {
         load(p);
 #pragma unroll
         for (int k = 0; k < SL; ++k)
 #pragma unroll
-            for (int half = 0; half < HALVES; ++half)
-#pragma unroll
-                for (int q = 0; q < 8; ++q) amax[half] = fmaxf(amax[half], fmaxf(fabsf(bf16_lo(w[k][half][q])), fabsf(bf16_hi(w[k][half][q]))));
+            for (int q = 0; q < 8; ++q) amax = fmaxf(amax, fmaxf(fabsf(bf16_lo(w[k][q])), fabsf(bf16_hi(w[k][q]))));
     }
-#pragma unroll
-    for (int half = 0; half < HALVES; ++half) {
-        amax[half] = fmaxf(amax[half], __shfl_xor(amax[half], 1, 64));
-        amax[half] = fmaxf(amax[half], __shfl_xor(amax[half], 2, 64));
-        if (c == 0) red[wave][r0 + 16 * half] = amax[half];
-    }
+    amax = fmaxf(amax, __shfl_xor(amax, 1, 64));
+    amax = fmaxf(amax, __shfl_xor(amax, 2, 64));
+    if (c == 0) red[wave][r0] = amax;
     __syncthreads();
-    float scale[HALVES];
-#pragma unroll
-    for (int half = 0; half < HALVES; ++half) {
-        const int r = r0 + 16 * half;
-        scale[half] = fmaxf(fmaxf(fmaxf(red[0][r], red[1][r]), fmaxf(red[2][r], red[3][r])), 1e-8f) / 448.0f;
-        if (wave == 0 && c == 0 && r < R) m.scales[32 * grp + r] = scale[half];
-    }
-    uint8_t *out = m.codes + 32 * grp * cols + (((c & 1) * 2 + (c >> 1)) * R + r0) * 16;
+    const float scale = fmaxf(fmaxf(fmaxf(red[0][r0], red[1][r0]), fmaxf(red[2][r0], red[3][r0])), 1e-8f) / 448.0f;
+    if (wave == 0 && c == 0 && row < R) m.scales[32 * grp + row] = scale;
+    uint8_t *const out = m.codes + 32 * grp * cols + (((c & 1) * 2 + (c >> 1)) * R + row) * 16;
+    const BlockDivisor divide(scale, true);
     for (int p = 0; p < passes; ++p) {
-        if (passes > 1) load(p);
+        if (!ONE) load(p);
 #pragma unroll
-        for (int k = 0; k < SL; ++k)
-#pragma unroll
-            for (int half = 0; half < HALVES; ++half) {
-                const int s = (p * SL + k) * 4 + wave, r = r0 + 16 * half;
-                if (s >= slices || r >= R) continue;
-                *(uint4 *)(out + (size_t)s * R * kSlice + half * 256) = quantise16(w[k][half], BlockDivisor(scale[half], true));
-            }
+        for (int k = 0; k < SL; ++k) {
+            const int s = (p * SL + k) * 4 + wave;
+            if (s < slices && row < R) *(uint4 *)(out + (size_t)s * R * kSlice) = quantise16(w[k], divide);
+        }
     }
 }
 
@@ -114,13 +93,10 @@ hipError_t launch_quantise_rows(const void *Xa, long rows_a, void *codes_a, floa
                                 float *scales_b, int cols, hipStream_t st)
 {
     const RowsIn a = {(const uint16_t *)Xa, rows_a, (uint8_t *)codes_a, scales_a}, b = {(const uint16_t *)Xb, rows_b, (uint8_t *)codes_b, scales_b};
-    const long groups = (rows_a + 31) / 32 + (rows_b + 31) / 32;
-    // fewer groups than two per CU: a workgroup takes half a group, twice as many CUs read and each waits for half the loads
-    if (groups < 512) {
-        if (cols <= 1024) quantise_rows_kernel<4, 1><<<(unsigned)(2 * groups), 256, 0, st>>>(a, b, cols);
-        else              quantise_rows_kernel<8, 1><<<(unsigned)(2 * groups), 256, 0, st>>>(a, b, cols);
-    } else if (cols <= 1024) quantise_rows_kernel<4, 2><<<(unsigned)groups, 256, 0, st>>>(a, b, cols);
-    else                     quantise_rows_kernel<8, 2><<<(unsigned)groups, 256, 0, st>>>(a, b, cols);
+    const unsigned grid = (unsigned)(2 * ((rows_a + 31) / 32 + (rows_b + 31) / 32));
+    if (cols <= 1024)      quantise_rows_kernel<4, true><<<grid, 256, 0, st>>>(a, b, cols);
+    else if (cols <= 2048) quantise_rows_kernel<8, true><<<grid, 256, 0, st>>>(a, b, cols);
+    else                   quantise_rows_kernel<8, false><<<grid, 256, 0, st>>>(a, b, cols);
     return hipGetLastError();
 }
 
