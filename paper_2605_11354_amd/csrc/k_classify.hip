@@ -708,13 +708,14 @@ __global__ __launch_bounds__(64) void select_kernel(const double *__restrict__ S
     classify_row_wave<KPL>(key, row, Nkb, k_c, k_n, hist, mbits, lab_pitch, lab_dense, crit_idx, Pc, sm_scale);
 }
 
-// Fused classifier for short rows (Nkb <= 64 KPL <= 256): block mean of Q, pooled logits and
+// Fused classifier for rows of 65 to 256 key blocks (Nkb <= 64 KPL): block mean of Q, pooled logits and
 // classification in one launch.  A workgroup of four waves takes four consecutive query blocks of one
 // (b, h).  Lane d of wave w first forms channel d of the block mean of query block w (serial fp64 sum
-// over the tokens in ascending order, times 1/count; the rows come in as whole 16-byte pieces through the wave's slice of LDS).  Chunk of 64 key blocks by chunk, the K means are staged in LDS
+// over the tokens in ascending order, times 1/count).  Chunk of 64 key blocks by chunk, the K means are staged in LDS
 // (the next chunk already on its way in registers) and lane l of wave w runs the 64-step fma chain of
-// (query block w, key block l), reading its K mean two channels per LDS access and channel d of the
-// Q mean out of lane d; the logits never leave registers.
+// (query block w, key block l), reading its K mean and (a broadcast) the Q mean two channels per LDS access; the logits never
+// leave registers.  (The Q mean out of lane d by v_readlane: 128 scalar registers, most of them spilt between the chunks.)
+// 16 heads x 172 rows of 172 key blocks: 17.4 -> 15.2 us; all loads of a block in flight: 0.3-0.5 us of it.
 template <int KPL, bool FP8>
 __global__ __launch_bounds__(256) void classify_fused_kernel(const void *__restrict__ Q, const float *__restrict__ sQ, RowMap rm,
                                                              const double *__restrict__ kbar, int N, int bq, int Nqb, int Nkb,
@@ -726,6 +727,7 @@ __global__ __launch_bounds__(256) void classify_fused_kernel(const void *__restr
     constexpr int kPitch = 66;             // doubles per row of the K-mean buffer: 16-byte aligned rows, and the
                                            // sixteen lanes of one 16-byte access pass cover all 64 banks once
     __shared__ __align__(16) double ks[64 * kPitch];
+    __shared__ __align__(16) double qm[4][kD];
     __shared__ __align__(16) uint32_t hist[4][256 + 64];   // per wave: a histogram and a spare word per lane
     // every kernel argument is fetched here, in one batch of scalar loads (left to the compiler: a dozen round trips to the
     // scalar cache, each in front of the first use of an argument)
@@ -749,63 +751,29 @@ __global__ __launch_bounds__(256) void classify_fused_kernel(const void *__restr
     load_chunk(0);
 
     double mean = 0.0;
-    if (rowok && KPL == 1) {
-        // Rows of at most 64 key blocks (frame attention): the block arrives 64 tokens at a time as whole rows (16-byte
-        // pieces, a wave instruction moves 1 KB of consecutive memory) into the wave's slice of the K-mean buffer, which
-        // is idle until the first chunk of K means is stored below; lane d then adds channel d of the tokens in
-        // ascending order (the order of the sum is part of the contract).  Rows past a ragged end repeat the last one
-        // and are not added.  (Measured: 18 % faster there; with more chunks of K means LDS is the busy unit and the
-        // direct loads below are faster.)
+    if (rowok) {                           // 2-byte (1-byte) loads straight from global memory: LDS is the busy unit here
         const int t0 = i * bq, cnt = min(bq, N - t0);
-        uint8_t *stg = (uint8_t *)ks + wave * 8192;
         double acc = 0.0;
+        // 64 tokens in flight at a time (sixteen, four round trips to memory per block: 3-5 % slower)
+        const uint8_t *x = (const uint8_t *)Q + (rm.head(bh) + (size_t)t0 * rm.ts + lane) * (FP8 ? 1 : 2);
+        const size_t step = (size_t)rm.ts * (FP8 ? 1 : 2);
         const double sc = FP8 ? (double)sQ[row] : 1.0;
-        for (int h0 = 0; h0 < cnt; h0 += 64) {
-            const int nrow = min(64, cnt - h0);
-            if (FP8) {
-                const uint8_t *x = (const uint8_t *)Q + rm.head(bh) + (size_t)(t0 + h0) * rm.ts + (lane & 3) * 16;
-                uint4 v[4];
+        auto token = [&](int t) -> uint32_t { return FP8 ? x[t * step] : *(const uint16_t *)(x + t * step); };
+        auto add = [&](uint32_t v) { acc += FP8 ? (double)__builtin_amdgcn_cvt_f32_fp8((int)v, 0) * sc : (double)bf16_bits_to_f32(v); };
+        int t = 0;
+        for (; t + 64 <= cnt; t += 64) {
+            uint32_t v[64];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) v[k] = *(const uint4 *)(x + (size_t)min((lane >> 2) + 16 * k, nrow - 1) * rm.ts);
+            for (int k = 0; k < 64; ++k) v[k] = token(t + k);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) *(uint4 *)(stg + ((lane >> 2) + 16 * k) * 64 + (lane & 3) * 16) = v[k];
-            } else {
-                const uint16_t *x = (const uint16_t *)Q + rm.head(bh) + (size_t)(t0 + h0) * rm.ts + (lane & 7) * 8;
-                uint4 v[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) v[k] = *(const uint4 *)(x + (size_t)min((lane >> 3) + 8 * k, nrow - 1) * rm.ts);
-#pragma unroll
-                for (int k = 0; k < 8; ++k) *(uint4 *)(stg + ((lane >> 3) + 8 * k) * 128 + (lane & 7) * 16) = v[k];
-            }
-            wave_lds_sync();
-            if (FP8) {
-#pragma unroll 16
-                for (int t = 0; t < nrow; ++t) acc += (double)__builtin_amdgcn_cvt_f32_fp8((int)stg[t * 64 + lane], 0) * sc;
-            } else {
-#pragma unroll 16
-                for (int t = 0; t < nrow; ++t) acc += (double)bf16_bits_to_f32(*(const uint16_t *)(stg + t * 128 + 2 * lane));
-            }
-            wave_lds_sync();               // the next 64 tokens overwrite the slice
+            for (int k = 0; k < 64; ++k) add(v[k]);
         }
-        mean = acc * (1.0 / (double)cnt);
-        if (qbar_out) qbar_out[row * kD + lane] = mean;
-    } else if (rowok) {                    // 2-byte (1-byte) loads straight from global memory: LDS is the busy unit here
-        const int t0 = i * bq, cnt = min(bq, N - t0);
-        double acc = 0.0;
-        if (FP8) {
-            const uint8_t *x = (const uint8_t *)Q + rm.head(bh) + (size_t)t0 * rm.ts + lane;
-            const double sc = (double)sQ[row];
 #pragma unroll 16
-            for (int t = 0; t < cnt; ++t) acc += (double)__builtin_amdgcn_cvt_f32_fp8((int)x[(size_t)t * rm.ts], 0) * sc;
-        } else {
-            const uint16_t *x = (const uint16_t *)Q + rm.head(bh) + (size_t)t0 * rm.ts + lane;
-#pragma unroll 16
-            for (int t = 0; t < cnt; ++t) acc += (double)bf16_bits_to_f32(x[(size_t)t * rm.ts]);
-        }
+        for (; t < cnt; ++t) add(token(t));
         mean = acc * (1.0 / (double)cnt);
         if (qbar_out) qbar_out[row * kD + lane] = mean;
     }
-    const int mlo = __double2loint(mean), mhi = __double2hiint(mean);
+    qm[wave][lane] = mean;
 
     uint64_t key[KPL];
 #pragma unroll
@@ -822,10 +790,9 @@ __global__ __launch_bounds__(256) void classify_fused_kernel(const void *__restr
 #pragma unroll
         for (int d = 0; d < kD; d += 2) {
             const double2 kv = *(const double2 *)(ks + lane * kPitch + d);
-            const double q0 = __hiloint2double(__builtin_amdgcn_readlane(mhi, d), __builtin_amdgcn_readlane(mlo, d));
-            const double q1 = __hiloint2double(__builtin_amdgcn_readlane(mhi, d + 1), __builtin_amdgcn_readlane(mlo, d + 1));
-            s = fma(q0, kv.x, s);
-            s = fma(q1, kv.y, s);
+            const double2 qv = *(const double2 *)(&qm[wave][d]);
+            s = fma(qv.x, kv.x, s);
+            s = fma(qv.y, kv.y, s);
         }
         const int j = m * 64 + lane;
         key[m] = ~0ull;
@@ -836,6 +803,148 @@ __global__ __launch_bounds__(256) void classify_fused_kernel(const void *__restr
     }
     if (rowok)
         classify_row_wave<KPL>(key, row, Nkb, k_c, k_n, hist[wave], mbits, lab_pitch, lab_dense, crit_idx, Pc, sm_scale);
+}
+
+// Rows of at most 64 key blocks (frame attention): the same three steps, a row per wave.  The wave brings the query block 64
+// tokens at a time as whole rows (16-byte pieces, a wave instruction moves 1 KB of consecutive memory; the next 64 are asked
+// for before these are added) through its slice of LDS, and lane d adds channel d in ascending order of the tokens (the order
+// of the sum is part of the contract; rows past a ragged end repeat the last one and are not added).  The K means of the head
+// then take the slices' place, the Q means lie beside them, and lane j runs the 64-step fma chain of key block j on broadcast
+// reads of the Q mean (instead of 128 v_readlane).  With one key per lane the rank of a key is a count: every key of the row
+// is read once by all (a broadcast) and compared, ties by block index -- the exact order at once, in a tenth of the
+// instructions of the radix descents that longer rows need.  KR: rows of the K-mean buffer; with 32 more workgroups fit a CU.
+// Against the radix form of this kernel: 2 heads x 8 rows 6.2 -> 4.2 us, 96 x 22 e4m3 11.5 -> 9.4, 128 x 22 bf16 12.4 -> 10.6,
+// 512 x 22 (90 MB of Q) 34 -> 29.7 us; there the sums, the chain and the ranks can each be left out without a change, it
+// waits for Q behind the writes of the states pass.  Two rows per wave (half the chains and ranks): 33.4 us.
+template <int KR, bool FP8>            // most key blocks of a row
+__global__ __launch_bounds__(256, 4) void classify_short_kernel(const void *__restrict__ Q, const float *__restrict__ sQ, RowMap rm,
+                                                             const double *__restrict__ kbar, int N, int bq, int Nqb, int Nkb,
+                                                             int k_c, int k_n, uint64_t *__restrict__ mbits, int lab_pitch,
+                                                             int8_t *__restrict__ lab_dense, int32_t *__restrict__ crit_idx,
+                                                             float *__restrict__ Pc, double *__restrict__ S_dense,
+                                                             double *__restrict__ qbar_out, float sm_scale)
+{
+    constexpr int kPitch = 66;             // doubles per row of the K-mean buffer (16-byte aligned rows, all banks)
+    constexpr int kSlice = 4096;                                                 // 64 (e4m3) or 32 (bf16) tokens of the wave's query block
+    constexpr int kBuf = 4 * kSlice > KR * kPitch * 8 ? 4 * kSlice : KR * kPitch * 8;
+    __shared__ __align__(16) uint8_t buf[kBuf];
+    __shared__ __align__(16) double qm[4][kD];                                   // Q means, then (as 64-bit words) the keys
+    asm volatile("" ::"s"(Q), "s"(sQ), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(kbar), "s"(N), "s"(bq), "s"(Nqb), "s"(Nkb), "s"(k_c), "s"(k_n),
+                 "s"(mbits), "s"(lab_pitch), "s"(lab_dense), "s"(crit_idx), "s"(Pc), "s"(S_dense), "s"(qbar_out), "s"(sm_scale));
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const long bh = blockIdx.y;
+    const int i = blockIdx.x * 4 + wave;                                         // the wave's query block
+    const long row = bh * Nqb + i;
+    const double *kh = kbar + bh * (long)Nkb * kD;
+
+    double2 nx[KR / 8];                    // K means on their way to LDS (two channels per lane and load)
+#pragma unroll
+    for (int r = 0; r < KR / 8; ++r) {
+        const int idx = tid + 256 * r, j = idx >> 5;
+        nx[r] = j < Nkb ? *(const double2 *)(kh + (long)j * kD + (idx & 31) * 2) : double2{0.0, 0.0};
+    }
+
+    // pieces of 64 tokens, one (bq = 64) or two (bq = 128)
+    constexpr int kLoads = FP8 ? 4 : 8;
+    const int pieces = bq >> 6;
+    uint32_t v[4 * kLoads];                                                      // (plain dwords: they stay in registers)
+    auto tokens = [&](int u, int &t0) {                                          // first token and number of tokens of a piece (below 1: none)
+        t0 = i * bq + 64 * u;
+        return min(64, N - t0);
+    };
+    auto load = [&](int u) {                                                     // (a piece without tokens repeats the last token)
+        int t0;
+        const int last = max(tokens(u, t0), 1) - 1;
+        const uint8_t *x = (const uint8_t *)Q + (rm.head(bh) + (size_t)min(t0, N - 1) * rm.ts) * (FP8 ? 1 : 2);
+        const size_t step = (size_t)rm.ts * (FP8 ? 1 : 2);
+#pragma unroll
+        for (int k = 0; k < kLoads; ++k) {
+            const uint4 w = FP8 ? *(const uint4 *)(x + min((lane >> 2) + 16 * k, last) * step + (lane & 3) * 16)
+                                : *(const uint4 *)(x + min((lane >> 3) + 8 * k, last) * step + (lane & 7) * 16);
+            v[4 * k] = w.x; v[4 * k + 1] = w.y; v[4 * k + 2] = w.z; v[4 * k + 3] = w.w;
+        }
+    };
+    uint8_t *stg = buf + wave * kSlice;
+    double acc = 0.0;
+    load(0);
+    for (int u = 0; u < pieces; ++u) {
+        int t0;
+        const int nrow = tokens(u, t0);
+        if (nrow > 0) {
+            const double sc = FP8 ? (double)sQ[row] : 1.0;
+            auto add = [&](int t) {
+                if (FP8) acc += (double)__builtin_amdgcn_cvt_f32_fp8((int)stg[t * 64 + lane], 0) * sc;
+                else     acc += (double)bf16_bits_to_f32(*(const uint16_t *)(stg + t * 128 + 2 * lane));
+            };
+            constexpr int kParts = FP8 ? 1 : 2, kTok = 64 / kParts;
+#pragma unroll
+            for (int part = 0; part < kParts; ++part) {
+                wave_lds_sync();           // the tokens before have been read
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int w = 16 * part + 4 * k;
+                    *(uint4 *)(stg + lane * 16 + 1024 * k) = make_uint4(v[w], v[w + 1], v[w + 2], v[w + 3]);
+                }
+                if (part == kParts - 1 && u + 1 < pieces) load(u + 1);
+                wave_lds_sync();
+                const int n = nrow - part * kTok;
+                if (n >= kTok) {
+#pragma unroll 32
+                    for (int t = 0; t < kTok; ++t) add(t);
+                } else {
+                    for (int t = 0; t < n; ++t) add(t);
+                }
+            }
+        }
+    }
+    const int cnt = min(bq, N - i * bq);
+    const double mean = cnt > 0 ? acc * (1.0 / (double)cnt) : 0.0;
+    qm[wave][lane] = mean;
+    if (qbar_out && cnt > 0) qbar_out[row * kD + lane] = mean;
+    __syncthreads();                       // every wave is done with its slice
+    double *ks = (double *)buf;
+#pragma unroll
+    for (int r = 0; r < KR / 8; ++r) {
+        const int idx = tid + 256 * r;
+        *(double2 *)(ks + (idx >> 5) * kPitch + (idx & 31) * 2) = nx[r];
+    }
+    __syncthreads();
+
+    const int j = lane, jr = min(j, KR - 1);
+    double s = 0.0;
+#pragma unroll 16
+    for (int d = 0; d < kD; d += 2) {
+        const double2 kv = *(const double2 *)(ks + jr * kPitch + d), qv = *(const double2 *)(&qm[wave][d]);
+        s = fma(qv.x, kv.x, s);
+        s = fma(qv.y, kv.y, s);
+    }
+    const bool valid = i < Nqb && j < Nkb;
+    if (S_dense && valid) S_dense[row * Nkb + j] = s;
+    const uint64_t key = valid ? desc_key(s) : ~0ull;
+    wave_lds_sync();                       // the Q means of this wave have been read
+    uint64_t *kk = (uint64_t *)&qm[wave][0];
+    kk[lane] = key;
+    wave_lds_sync();
+
+    int rank = 0;                          // blocks of the row in front of this one
+#pragma unroll 4
+    for (int t = 0; t < Nkb; ++t) {
+        const uint64_t o = kk[t];
+        rank += (o < key || (o == key && t < j)) ? 1 : 0;
+    }
+    if (Pc) {                              // compressed block-score softmax (fp32 output)
+        const double s_max = key_to_logit(wave_min_u64(key));
+        const float e = valid ? __expf((float)((s - s_max) * (double)sm_scale)) : 0.f;
+        const float sum = wave_sum(e);
+        if (valid) Pc[row * Nkb + j] = e * (1.f / sum);
+    }
+    const bool crit = valid && rank < k_c;
+    const int8_t lab = crit ? 2 : (rank < Nkb - k_n ? 1 : 0);
+    const uint64_t mb = __ballot(valid && lab == 1), cb = __ballot(crit);
+    if (!valid) return;
+    if (j == 0) mbits[row * (lab_pitch >> 6)] = mb;
+    if (lab_dense) lab_dense[row * Nkb + j] = lab;
+    if (crit_idx && crit) crit_idx[row * k_c + (int)__popcll(cb & ((1ull << j) - 1))] = j;
 }
 
 // ---- workgroup-per-row variant for long rows (Nkb > 256) ------------------------------------
@@ -1102,7 +1211,13 @@ hipError_t launch_classify_fused(const void *Q, const float *sQ, bool fp8, RowMa
 {
     const int Nqb = (N + bq - 1) / bq;
 #define SLA_CF(K) return launch_classify_fused_t<K>(Q, sQ, fp8, rm, kbar, BH, N, bq, Nqb, Nkb, k_c, k_n, mbits, lab_pitch, lab_dense, crit_idx, Pc, S_dense, qbar_out, sm_scale, st)
-    if (Nkb <= 64) SLA_CF(1);
+    if (Nkb <= 64) {                       // one key per lane: ranks by counting (longer rows: radix descents, below)
+#define SLA_CS(KR, F8) classify_short_kernel<KR, F8><<<dim3((Nqb + 3) / 4, BH), 256, 0, st>>>(Q, sQ, rm, kbar, N, bq, Nqb, Nkb, k_c, k_n, mbits, lab_pitch, lab_dense, crit_idx, Pc, S_dense, qbar_out, sm_scale)
+        if (Nkb <= 32) { if (fp8) SLA_CS(32, true); else SLA_CS(32, false); }
+        else           { if (fp8) SLA_CS(64, true); else SLA_CS(64, false); }
+        return hipGetLastError();
+    }
+#undef SLA_CS
     if (Nkb <= 128) SLA_CF(2);
     if (Nkb <= 192) SLA_CF(3);
     if (Nkb <= 256) SLA_CF(4);
