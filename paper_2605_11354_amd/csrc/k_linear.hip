@@ -448,10 +448,10 @@ hipError_t launch_gemm(const void *A8, const float *sa, const void *W8, const fl
 hipError_t launch_fp8_gemm(const void *A8, const float *sa, const void *W8, const float *sw, const void *bias, int M, int O, int K,
                            void *Y, hipStream_t st)
 {
-    // else the widest tile that still gives every CU two workgroups: 1374 tokens x 1024 -> 3072 take 11.5 us with 64-token tiles
-    // (528 of them) where 128-token tiles (264) took 18
+    // 128-token tiles from 400 of them on: 420 tiles (2600 x 1920 -> 2496) take 27.5 us, their halves 31.8; 448 (3500 x 2048 ->
+    // 2048) 30.5 against 33.8; 384 (2000 x 1024 -> 3072) the same; 264 (1374 x 1024 -> 3072) 19.3 against 18.8
     if (lin_wide_tiles(M, O)) return launch_gemm<4, false>(A8, sa, W8, sw, bias, M, O, K, Y, QkvOut{}, st);
-    if ((long)((M + 127) / 128) * ((O + 127) / 128) >= 512) return launch_gemm<2, false>(A8, sa, W8, sw, bias, M, O, K, Y, QkvOut{}, st);
+    if ((long)((M + 127) / 128) * ((O + 127) / 128) >= 400) return launch_gemm<2, false>(A8, sa, W8, sw, bias, M, O, K, Y, QkvOut{}, st);
     return launch_gemm<1, false>(A8, sa, W8, sw, bias, M, O, K, Y, QkvOut{}, st);
 }
 
