@@ -31,11 +31,9 @@
 // value pins below hold the order).  Everything with control flow (raising the maximum, the first unit of a row, a
 // ragged key block, a key block whose V scale is far below the first one's) sits between the steps or in the
 // "careful" variant of a step.  In the middle of a list, where none of the special cases can occur (one bit per list
-// entry says so), iterations run in a form without guards, and, where |q| max|k| bounds the exponents of the wave's rows,
-// without looking at the maximum at all.  What bounds the kernel: the issue of vector instructions beside the MFMA (326
-// cycles for a unit's instructions in a register-only loop at two waves per SIMD, 256 of them MFMA), and on long bf16
-// launches the clock the chip grants (1.5 GHz).  Without the overflow checks and the dot-product row sums, at two ring
-// slots for 64-row blocks: 16 heads x 10992 tokens, lists of 9: 74 -> 61 us; 43968 tokens, lists of 34, bf16: 0.60 -> 0.54 ms;
+// entry says so), iterations run in a form without guards.  What bounds the kernel: the issue of vector instructions beside
+// the MFMA, and on long bf16 launches the clock the chip grants (1.5 GHz).  Without the dot-product row sums (see lsum), at two
+// ring slots for 64-row blocks: 16 heads x 10992 tokens, lists of 9: 74 -> 61 us; 43968 tokens, lists of 34, bf16: 0.60 -> 0.54 ms;
 // 137400 tokens, lists of 64, e4m3: 2.54 -> 2.35 ms.
 //
 // Memory pipeline.  K and V^T tiles go from global memory straight into LDS (global_load_lds_dwordx4, no staging
@@ -70,11 +68,6 @@ constexpr float kRaise = 12.0f;
 // careful step: its weights (or the factor that divides the scale out of the row sums again) would leave the range
 // of fp16, so its row sums are formed in fp32.
 constexpr float kTinyV = 8.0f;
-
-// Rows whose exponents are bounded skip the overflow check (see bounded_rows below): weights at most 2^kTopW, at most
-// kDrop binades below their place under the exact maximum of the units seen so far.
-constexpr float kTopW = 15.0f;
-constexpr float kDrop = 6.0f;
 
 typedef __attribute__((address_space(3))) void *lds_void_p;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
@@ -355,21 +348,15 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     }
     // the scales of the window's blocks: a gather that depends on the indices (the first tile copies are requested
     // between the two, see the prologue)
-    // w_kc, w_lv: over the window's valid entries, the largest |K row| times exp2 constant and the largest log2 V scale
-    // relative to the first tile's.  |q| w_kc + w_lv bounds the exponent of every weight of a row (Cauchy-Schwarz).
-    float w_kc = 0.f, w_lv = 0.f;
     auto load_window_scales = [&](bool first) __attribute__((always_inline)) {
-        float2 vk = vkh[d_j];
+        float lv = vkh[d_j].x;
         // exp2 constant of the tile: softmax scale * log2(e) (* Q and K block scales for e4m3)
         d_cj = FP8 ? fmaxf(c_exp * qscale * sK[bh * Nkb + d_j], 1e-30f) : c_exp;
-        asm volatile("" : "+v"(vk.x), "+v"(vk.y), "+v"(d_cj));       // the loads complete here, not at some later first use
+        asm volatile("" : "+v"(lv), "+v"(d_cj));       // the loads complete here, not at some later first use
         // log2 of the V scale of the first tile: the reference of the weights
-        if (first) lv_ref = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(vk.x)));
-        d_lv = vk.x - lv_ref;
-        const bool in = wbase + lane < k;
-        d_bad = __ballot(!in || d_j == ragged_j || !(fabsf(d_lv) <= kTinyV));
-        w_kc = wave_max_dpp(in ? vk.y * d_cj : 0.f);
-        w_lv = wave_max_dpp(in ? d_lv : -INFINITY);
+        if (first) lv_ref = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(lv)));
+        d_lv = lv - lv_ref;
+        d_bad = __ballot(wbase + lane >= k || d_j == ragged_j || !(fabsf(d_lv) <= kTinyV));
     };
     auto load_window = [&](int wb) __attribute__((always_inline)) {
         const int idx = wb + lane;
@@ -566,22 +553,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     VFrag vf_use, vf_pre;
     TileInfo t_cur, t_nxt;
     const int U = 2 * k;                               // units of this wave
-    // norm of the lane's query row, from above (e4m3: of the codes, the scale is in the tile's exp2 constant)
-    float qnorm = 0.f;
-    if (FP8) {
-#pragma unroll
-        for (int w = 0; w < 8; ++w) {
-            const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8(q8[w], false), hi = __builtin_amdgcn_cvt_pk_f32_fp8(q8[w], true);
-            qnorm = fmaf(lo[0], lo[0], fmaf(lo[1], lo[1], fmaf(hi[0], hi[0], fmaf(hi[1], hi[1], qnorm))));
-        }
-    } else {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const uint4 w = __builtin_bit_cast(uint4, qf[s]);
-            qnorm = dot2_bf16(w.x, w.x, dot2_bf16(w.y, w.y, dot2_bf16(w.z, w.z, dot2_bf16(w.w, w.w, qnorm))));
-        }
-    }
-    qnorm = norm_from_above(qnorm + xchg32(qnorm));
     if (k > 0) {
         t_cur = tile_info(0);
         s_cur = compute_S(load_kfrag(0, unit_half(0)), t_cur.valid == kBK ? zero16 : s_init(t_cur.valid, unit_half(0)));
@@ -622,7 +593,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     // that open a new accumulator at the end of the block, and the exponentials behind them), and in a scheduling
     // barrier for the later passes.  The running maximum stays where it is.  The step ends with the overflow check of
     // the next unit, while the last MFMA runs.
-    auto fast_step = [&](bool checked, const TileInfo &t, const TileInfo &tn, int cv, int hv, int ck, int hk) __attribute__((always_inline)) {
+    auto fast_step = [&](const TileInfo &t, const TileInfo &tn, int cv, int hv, int ck, int hk) __attribute__((always_inline)) {
         f32x16 s_nxt = zero16;
         Weights w;
         vf_pre = load_vfrag(cv, hv);
@@ -701,7 +672,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
         w.p[0] = __builtin_bit_cast(f16x8, make_uint4(pw[0], pw[1], pw[2], pw[3]));
         w.p[1] = __builtin_bit_cast(f16x8, make_uint4(pw[4], pw[5], pw[6], pw[7]));
         w.inv2 = t.inv2;
-        if (checked) over_cur = overflows(s_nxt, tn);
+        over_cur = overflows(s_nxt, tn);
         // the fragments requested at the top of this step have long arrived: say so here, so that the wait the
         // compiler places in front of their first use in the next step does not also cover that step's own reads
         __builtin_amdgcn_s_waitcnt(0xC07F);        // lgkmcnt(0) only
@@ -709,9 +680,14 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     };
 #undef SLA_PIN
 
-    // Sets the reference exponent of the rows to m_new (never below the present one) between two steps: the accumulators,
-    // the row sums and the weights of the previous unit (not yet multiplied into the accumulators) are rescaled.
-    auto raise_to = [&](float m_new) __attribute__((always_inline)) {
+    // Raises the running maximum of the rows to the exact maximum over the unit whose S^T is s_cur, in front of a fast
+    // step: the accumulators, the row sums and the weights of the previous unit (not yet multiplied into the accumulators)
+    // are rescaled; the fast step that follows then sees no exponent above zero.  (The reference is never above the exact
+    // maximum of the units seen: fp16 keeps a weight's bits down to 2^-14 of it.  Raised ahead by a bound |q| max|k|, so that
+    // the overflow checks could be left out, small weights lost bits, and every move of the window raised it again.  Keeping the
+    // checks costs nothing: a layer of 16 heads x 43968 tokens 656 us with and 658 without them, 10992 tokens 98 and 99.)
+    auto raise_reference = [&](const TileInfo &t) __attribute__((always_inline)) {
+        const float m_new = fmaxf(m_run, pair_max(max16(s_cur)) * t.cj + t.lsv);
         const float alpha = m_new == m_run ? 1.0f : fast_exp2(m_run - m_new);
         rescale(alpha);
         const _Float16 ah = (_Float16)alpha;
@@ -720,21 +696,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
 #pragma unroll
             for (int x = 0; x < 8; ++x) w_prev.p[ss][x] *= ah;
         m_run = m_new;
-    };
-    // In front of a fast step on a unit that would overflow: to the exact maximum over the unit whose S^T is s_cur; the
-    // fast step that follows then sees no exponent above zero.
-    auto raise_reference = [&](const TileInfo &t) __attribute__((always_inline)) { raise_to(fmaxf(m_run, pair_max(max16(s_cur)) * t.cj + t.lsv)); };
-    // Whether the exponents of all the wave's rows are bounded so tightly by |q| max |k| that no unit of the window needs
-    // the overflow check: the reference is then raised once, to where the bound makes the largest possible weight 2^kTopW
-    // (fp16 holds 2^15.99).  Not if that is more than kDrop above the exact maximum seen so far: a weight of the largest
-    // exponent seen would then be below 2^-kDrop, and fp16 keeps its full precision down to 2^-14 only.  With
-    // kDrop = 6 weights 2^-8 of the largest and more still have all their bits, smaller ones an error of 2^-19 of the largest.
-    // The check is 11 of the 62 vector instructions of a unit, and it ends every step with a vote on the last MFMA's result.
-    auto bounded_rows = [&]() __attribute__((always_inline)) {
-        const float m_need = fmaf(qnorm, w_kc, w_lv) - kTopW;
-        if (__ballot(!(m_need <= m_run + kDrop)) != 0) return false;
-        if (__ballot(m_need > m_run) != 0) raise_to(fmaxf(m_run, m_need));
-        return true;
     };
 
     // Ring bookkeeping.  During iteration c the LDS reads touch V^T tile c and K tile c+1 (the fragments of the following
@@ -768,7 +729,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
         if (over_cur || c == 0 || t_cur.tiny || t_cur.valid != kBK) careful_step(c > 0, true, t_cur, t_cur, 1, vslot, 0, kslot, 0);
         else {
             set_ones(w_prev.inv2);
-            fast_step(true, t_cur, t_cur, vslot, 0, kslot, 0);
+            fast_step(t_cur, t_cur, vslot, 0, kslot, 0);
         }
         SLA_T(c, 3);
         // second half of tile c: accumulates its first half, forms S^T of the first half of tile c+1;
@@ -776,16 +737,15 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
         if (over_cur || !more || t_cur.tiny || t_nxt.valid != kBK) careful_step(true, more, t_cur, t_nxt, 0, vslot, 1, kslot, 1);
         else {
             set_ones(w_prev.inv2);
-            fast_step(true, t_cur, t_nxt, vslot, 1, kslot, 1);
+            fast_step(t_cur, t_nxt, vslot, 1, kslot, 1);
         }
         SLA_T(c, 4);
         t_cur = t_nxt;
     };
     // The lean form, for the middle of a list: tile c is not the first, tiles c and c+1 are full, neither has a far-off V
-    // scale, and the window holds them.  Nothing is conditional but (checked) the raise of the running maximum; both steps
-    // are fast steps.  Requests past the end of the list repeat its last tile into slots nobody reads any more, so that the
+    // scale, and the window holds them.  Nothing is conditional but the raise of the running maximum; both steps are fast steps.  Requests past the end of the list repeat its last tile into slots nobody reads any more, so that the
     // number of copies in flight stays the same to the end; the last tile's guarded iteration waits for them.
-    auto lean_iteration = [&](bool checked, int c, auto phase) __attribute__((always_inline)) {
+    auto lean_iteration = [&](int c, auto phase) __attribute__((always_inline)) {
         constexpr int P = decltype(phase)::value;
         constexpr uint32_t kreq = P * T::KBYTES, vreq = ((P + SL - 1) % SL) * T::VBYTES;
         constexpr int kslot = ((P + 1) % SL) * T::KBYTES, vslot = T::VRING + P * T::VBYTES;
@@ -800,11 +760,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
         t_nxt.inv2 = inv2_of(t_nxt.lsv);
         SLA_T(c, 2);
         if (over_cur) raise_reference(t_cur);
-        fast_step(checked, t_cur, t_cur, vslot, 0, kslot, 0);
+        fast_step(t_cur, t_cur, vslot, 0, kslot, 0);
         SLA_T(c, 3);
         if (over_cur) raise_reference(t_cur);
         set_ones(t_cur.inv2);                          // the units accumulated from here on are this tile's
-        fast_step(checked, t_cur, t_nxt, vslot, 1, kslot, 1);
+        fast_step(t_cur, t_nxt, vslot, 1, kslot, 1);
         SLA_T(c, 4);
         t_cur = t_nxt;
     };
@@ -816,15 +776,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
         const int e = c + run - 1;
         return k - wbase > 64 ? min(e, wbase + 64 - KAHEAD) : e;
     };
-    // The lean loop, unrolled over the ring phase so that slots are constants; entered at phase 1, left at phase 1.
-    auto lean_loop = [&](bool checked, int &c, int end) __attribute__((always_inline)) {
-        do {
-            lean_iteration(checked, c, std::integral_constant<int, 1>{});
-            if constexpr (SL == 3) lean_iteration(checked, c + 1, std::integral_constant<int, 2>{});
-            lean_iteration(checked, c + SL - 1, std::integral_constant<int, 0>{});
-            c += SL;
-        } while (c + SL <= end);
-    };
     for (int c = 0, P = 0; c < k;) {
         iteration(c, P);
         ++c;
@@ -832,10 +783,13 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
         if (P == 1 && c + KAHEAD <= k) {       // (the guarded iteration before made a full set of requests)
             const int end = lean_end(c);
             if (c + SL <= end) {
-                const bool checked = !bounded_rows();
-                if (!checked) over_cur = false;          // the bound covers the window, and with it the next unit
                 set_ones(w_prev.inv2);
-                lean_loop(checked, c, end);
+                do {                           // unrolled over the ring phase so that slots are constants; entered and left at phase 1
+                    lean_iteration(c, std::integral_constant<int, 1>{});
+                    if constexpr (SL == 3) lean_iteration(c + 1, std::integral_constant<int, 2>{});
+                    lean_iteration(c + SL - 1, std::integral_constant<int, 0>{});
+                    c += SL;
+                } while (c + SL <= end);
             }
         }
     }

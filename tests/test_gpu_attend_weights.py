@@ -1,0 +1,92 @@
+"""The softmax weights of the attention kernel (Alg. 1 steps 4-5) where 16 bits could lose them, against the oracle on the
+fp32 result: rows with one dominant key of no value, and long lists whose keys grow from one window of 64 entries to the
+next in directions the queries do not see."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_11354_amd import binding as B
+from paper_2605_11354_amd import synth
+from tests import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(q, k, v, bq, dtype):
+    """Every key block critical.  q, k, v: float [N,64]."""
+    N = q.shape[0]
+    cfg = synth.CONFIGS[1].with_(B=1, H=1, N=N, bq=bq, dtype=dtype, proj_per_head=False)
+    d = {"Q": synth.to_bf16_bits(q)[None, None], "K": synth.to_bf16_bits(k)[None, None], "V": synth.to_bf16_bits(v)[None, None],
+         "W": synth.to_bf16_bits(np.eye(64))[None], "sQ": None, "sK": None, "sV": None}
+    if dtype == "fp8":
+        for t, blk in (("Q", bq), ("K", 64), ("V", 64)):
+            d[t], d["s" + t] = synth.quantise_e4m3_blocks(d[t], blk)
+    d = {n: None if a is None else np.ascontiguousarray(a) for n, a in d.items()}
+    Nkb = -(-N // 64)
+    return G.Case(cfg, d, k_crit=Nkb, k_neg=0)
+
+
+def _sparse_f32(case, lab):
+    O = torch.full((1, 1, case.cfg.N, 64), float("nan"), dtype=torch.float32, device="cuda")
+    B.sla_sparse_combine_f32(case.p, case.Q, case.K, case.V, None, torch.from_numpy(lab).cuda(), None, O, case.sQ, case.sK, case.sV, case.ws)
+    torch.cuda.synchronize()
+    return O.cpu().numpy().astype(np.float64)
+
+
+def _error(case, oracle, lab, sel):
+    """Largest error of the sparse output over the blocks of sel, relative to its RMS."""
+    ref = case.oracle_attend(oracle, lab, sel=sel, want_parts=True)
+    got = G.gather_blocks(_sparse_f32(case, lab), sel, case.cfg.bq, 1)
+    return float(np.abs(got - ref["O_sparse"]).max() / np.sqrt(np.mean(ref["O_sparse"] ** 2)))
+
+
+@pytest.mark.parametrize("bq", [64, 128])
+@pytest.mark.parametrize("above", [1.0, 3.0, 4.5])      # of |q| max|k| over the largest exponent plus 15, in binades
+def test_small_weights_under_a_dominant_key(oracle, bq, above):
+    """A key of zero V at exponent 17, all others near 2^-17 of its weight: fp16 holds such weights in steps of 2^-24 of the
+    largest, an error of at most 2^-25 each.  Uniform errors on n weights against the weights' own 2-norm (at least
+    2^-17 sqrt(n)): 2^-25 / sqrt(3) / 2^-17 = 2.3e-3 RMS, five times that for the largest of 140000 values, and the weights
+    above 2^-14, in whole fp16 precision, add 2^-11 at most.  A reference some binades above the largest weight multiplies
+    the first by two for each of them."""
+    rng = np.random.default_rng(int(above) + bq)
+    N, c = 34 * 64, 0.125 * np.log2(np.e)
+    q = np.zeros((N, 64))
+    q[:, 0] = 8.0
+    peak = 17.0 / (8.0 * c)
+    k = np.zeros((N, 64))
+    k[:, 0] = (0.0 + rng.standard_normal(N)) / (8.0 * c)
+    k[7, 0] = peak
+    side = rng.standard_normal((N, 63))
+    length = (17.0 + 15.0 + above) / (8.0 * c)
+    k[:, 1:] = side / np.linalg.norm(side, axis=1, keepdims=True) * np.sqrt(length ** 2 - k[:, :1] ** 2)
+    v = rng.standard_normal((N, 64))
+    v[7] = 0.0
+    case = _case(q, k, v, bq, "bf16")
+    lab = np.full((1, 1, case.Nqb, case.Nkb), 2, np.int8)
+    err = _error(case, oracle, lab, [(0, 0), (0, case.Nqb - 1)])
+    print(f"bq={bq} above={above}: {err:.3e}")
+    assert err <= 1.2e-2
+
+
+@pytest.mark.parametrize("bq,dtype", [(64, "bf16"), (128, "bf16"), (64, "fp8"), (128, "fp8")])
+def test_keys_that_grow_along_the_list(oracle, bq, dtype):
+    """256 critical blocks, |k| growing by a quarter every 32 blocks in channels where q is zero, logits near zero: all keys
+    weigh about the same.  Values of 1 in the last 64 blocks and of 1/4 before, so that the output tells their share of the
+    weight."""
+    rng = np.random.default_rng(bq)
+    N, c = 256 * 64, 0.125 * np.log2(np.e)
+    q = np.zeros((N, 64))
+    q[:, :8] = rng.standard_normal((N, 8))
+    q[:, :8] *= 8.0 / np.linalg.norm(q[:, :8], axis=1, keepdims=True)
+    k = np.zeros((N, 64))
+    k[:, :8] = 0.2 * rng.standard_normal((N, 8))
+    side = rng.standard_normal((N, 56))
+    length = 14.0 + 3.8 * np.maximum(np.arange(N) // 2048 - 1, 0)
+    k[:, 8:] = side / np.linalg.norm(side, axis=1, keepdims=True) * length[:, None]
+    v = np.full((N, 64), 0.25)
+    v[192 * 64:] = 1.0
+    case = _case(q, k, v, bq, dtype)
+    lab = np.full((1, 1, case.Nqb, case.Nkb), 2, np.int8)
+    err = _error(case, oracle, lab, [(0, 0), (0, case.Nqb - 1)])
+    print(f"bq={bq} {dtype}: {err:.3e}")
+    assert err <= 2e-3                                   # fp16 weights (2^-11) on a sum that cancels nothing
