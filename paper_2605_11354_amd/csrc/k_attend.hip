@@ -19,7 +19,7 @@
 //
 // Arithmetic of the weights.  P is rounded to fp16 (11 significant bits) and V^T arrives as fp16 from the states
 // kernel (bf16 or E4M3 values are exact in fp16 once divided by the power of two the states kernel picks per key
-// block; its base-2 logarithm comes in `vks` and is added to the exponent of the weights, so the product is
+// block; its base-2 logarithm comes in `lvs` and is added to the exponent of the weights, so the product is
 // unchanged).  The second product runs on the fp16 MFMA at the rate of the bf16 one with an eighth of the rounding
 // error on the weights.  That margin pays for a running maximum that is only raised when a lane sees an exponent
 // above kRaise: the accumulators are rescaled a few times per row instead of once per tile, and the softmax of a
@@ -222,7 +222,7 @@ __device__ unsigned long long sla_probe_times[64 * 8];
 // SL: ring slots (two or three, see above).
 template <int NW, bool FP8, int SL>
 __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
-    const void *__restrict__ Qp, const void *__restrict__ Kp, const uint16_t *__restrict__ Vp, const float2 *__restrict__ vks,
+    const void *__restrict__ Qp, const void *__restrict__ Kp, const uint16_t *__restrict__ Vp, const float *__restrict__ lvs,
     const float *__restrict__ sQ, const float *__restrict__ sK, RowMap rm,
     const int32_t *__restrict__ crit_idx, int k_c, const uint16_t *__restrict__ Hq, const uint16_t *__restrict__ WT,
     int proj_per_head, int phi, int H, int N, int Nqb, int Nkb, long total, float c_exp, uint16_t *__restrict__ O, float *__restrict__ O32)
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     __shared__ __attribute__((aligned(1024))) uint8_t lds[T::LDS];
     // All kernel arguments are fetched here, in one batch of scalar loads: left to the compiler each would be loaded in
     // front of its first use, a dozen scalar-cache round trips one after the other along the prologue and the epilogue.
-    asm volatile("" ::"s"(Qp), "s"(Kp), "s"(Vp), "s"(vks), "s"(sQ), "s"(sK), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(crit_idx),
+    asm volatile("" ::"s"(Qp), "s"(Kp), "s"(Vp), "s"(lvs), "s"(sQ), "s"(sK), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(crit_idx),
                  "s"(k_c), "s"(Hq), "s"(WT), "s"(proj_per_head), "s"(phi), "s"(H), "s"(N), "s"(Nqb), "s"(Nkb), "s"(total), "s"(c_exp), "s"(O), "s"(O32));
     const long work = xcd_remap(blockIdx.x, total);
     if (work >= total) return;                        // the whole workgroup leaves together
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     const int krowb = rm.ts * ES;                     // bytes between consecutive K rows
     const uint8_t *Kh = (const uint8_t *)Kp + head * ES;
     const uint8_t *Vh = (const uint8_t *)(Vp + (size_t)bh * Nkb * kBK * kD);
-    const float2 *vkh = vks + bh * Nkb;
+    const float *lvh = lvs + bh * Nkb;
 
     SLA_TP(62, 0);
     // The critical list of the row is asked for first of all: the tile copies, the scale gather and with them the whole
@@ -349,7 +349,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     // the scales of the window's blocks: a gather that depends on the indices (the first tile copies are requested
     // between the two, see the prologue)
     auto load_window_scales = [&](bool first) __attribute__((always_inline)) {
-        float lv = vkh[d_j].x;
+        float lv = lvh[d_j];
         // exp2 constant of the tile: softmax scale * log2(e) (* Q and K block scales for e4m3)
         d_cj = FP8 ? fmaxf(c_exp * qscale * sK[bh * Nkb + d_j], 1e-30f) : c_exp;
         asm volatile("" : "+v"(lv), "+v"(d_cj));       // the loads complete here, not at some later first use
@@ -960,7 +960,7 @@ constexpr int kShortList = 2;
 // workgroup then lives 20 us instead of 31, but only four fit a CU instead of eight, and the launch takes the same time.)
 template <int NW, bool FP8>
 __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
-    const void *__restrict__ Qp, const void *__restrict__ Kp, const uint16_t *__restrict__ Vp, const float2 *__restrict__ vks,
+    const void *__restrict__ Qp, const void *__restrict__ Kp, const uint16_t *__restrict__ Vp, const float *__restrict__ lvs,
     const float *__restrict__ sQ, const float *__restrict__ sK, RowMap rm,
     const int32_t *__restrict__ crit_idx, int k_c, const uint16_t *__restrict__ Hq, const uint16_t *__restrict__ WT,
     int proj_per_head, int phi, int H, int N, int Nqb, int Nkb, long total, float c_exp, uint16_t *__restrict__ O, float *__restrict__ O32)
@@ -970,7 +970,7 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
     constexpr int KROWB = FP8 ? 64 : 128;
     constexpr int kA = 0, kB = 8192, kZ = 16384;      // LDS: slot A (K tile / Hq^T), slot B (V^T tile / W^T), the Z row
     __shared__ __attribute__((aligned(1024))) uint8_t lds[kZ + 256];
-    asm volatile("" ::"s"(Qp), "s"(Kp), "s"(Vp), "s"(vks), "s"(sQ), "s"(sK), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(crit_idx),
+    asm volatile("" ::"s"(Qp), "s"(Kp), "s"(Vp), "s"(lvs), "s"(sQ), "s"(sK), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(crit_idx),
                  "s"(k_c), "s"(Hq), "s"(WT), "s"(proj_per_head), "s"(phi), "s"(H), "s"(N), "s"(Nqb), "s"(Nkb), "s"(total), "s"(c_exp), "s"(O), "s"(O32));
     const long work = xcd_remap(blockIdx.x, total);
     if (work >= total) return;
@@ -1029,7 +1029,7 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
     int k = okm == ~0ull ? 64 : __builtin_ctzll(~okm);
     k = __builtin_amdgcn_readfirstlane(min(k, k_c));
     const int d_j = jok ? j0 : 0;
-    float d_lv = vks[bh * Nkb + d_j].x;
+    float d_lv = lvs[bh * Nkb + d_j];
     float d_cj = FP8 ? fmaxf(c_exp * qscale * sK[bh * Nkb + d_j], 1e-30f) : c_exp;
     asm volatile("" : "+v"(d_lv), "+v"(d_cj));
     const float lv_ref = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(d_lv)));
@@ -1262,17 +1262,17 @@ hipError_t launch_transpose_w(const void *W, int nW, void *WT, hipStream_t st)
 }
 
 template <int NW, bool FP8, int SL = 3>
-static hipError_t launch_attend_t(const void *Q, const void *K, const void *Vp, const float2 *vks, const float *sQ, const float *sK, RowMap rm,
+static hipError_t launch_attend_t(const void *Q, const void *K, const void *Vp, const float *lvs, const float *sQ, const float *sK, RowMap rm,
                                   const int32_t *crit_idx, int k_c, const void *Hq, const void *WT, int proj_per_head, int phi,
                                   int H, int N, int Nqb, int Nkb, long total, float c_exp, void *O, float *O32, hipStream_t st)
 {
-    attend_kernel<NW, FP8, SL><<<(unsigned)xcd_grid(total), 64 * NW, 0, st>>>(Q, K, (const uint16_t *)Vp, vks, sQ, sK, rm, crit_idx, k_c, (const uint16_t *)Hq,
+    attend_kernel<NW, FP8, SL><<<(unsigned)xcd_grid(total), 64 * NW, 0, st>>>(Q, K, (const uint16_t *)Vp, lvs, sQ, sK, rm, crit_idx, k_c, (const uint16_t *)Hq,
                                                                      (const uint16_t *)WT, proj_per_head, phi, H, N, Nqb, Nkb,
                                                                      total, c_exp, (uint16_t *)O, O32);
     return hipGetLastError();
 }
 
-hipError_t launch_attend(const void *Q, const void *K, const void *Vp, const float2 *vks,
+hipError_t launch_attend(const void *Q, const void *K, const void *Vp, const float *lvs,
                          const float *sQ, const float *sK, bool fp8, RowMap rm,
                          const int32_t *crit_idx, int k_c, const void *Hq, const void *WT,
                          int proj_per_head, int phi, int B, int H, int N, int bq, float sm_scale,
@@ -1281,13 +1281,13 @@ hipError_t launch_attend(const void *Q, const void *K, const void *Vp, const flo
     const int Nqb = (N + bq - 1) / bq, Nkb = (N + kBK - 1) / kBK;
     const long total = (long)B * H * Nqb;
     const float c_exp = sm_scale * kLog2e;
-#define SLA_ATT(NW, F8, SL) return launch_attend_t<NW, F8, SL>(Q, K, Vp, vks, sQ, sK, rm, crit_idx, k_c, Hq, WT, proj_per_head, phi, H, N, Nqb, Nkb, total, c_exp, O, O32, st)
+#define SLA_ATT(NW, F8, SL) return launch_attend_t<NW, F8, SL>(Q, K, Vp, lvs, sQ, sK, rm, crit_idx, k_c, Hq, WT, proj_per_head, phi, H, N, Nqb, Nkb, total, c_exp, O, O32, st)
     if (bq == 128) { if (fp8) SLA_ATT(4, true, 3); else SLA_ATT(4, false, 3); }
     // lists of at most two blocks (frame attention): the kernel without a pipeline, eight workgroups per CU
     if (k_c <= kShortList) {
-        if (fp8) attend_short_kernel<2, true><<<(unsigned)xcd_grid(total), 128, 0, st>>>(Q, K, (const uint16_t *)Vp, vks, sQ, sK, rm, crit_idx, k_c, (const uint16_t *)Hq,
+        if (fp8) attend_short_kernel<2, true><<<(unsigned)xcd_grid(total), 128, 0, st>>>(Q, K, (const uint16_t *)Vp, lvs, sQ, sK, rm, crit_idx, k_c, (const uint16_t *)Hq,
                                                                                        (const uint16_t *)WT, proj_per_head, phi, H, N, Nqb, Nkb, total, c_exp, (uint16_t *)O, O32);
-        else attend_short_kernel<2, false><<<(unsigned)xcd_grid(total), 128, 0, st>>>(Q, K, (const uint16_t *)Vp, vks, sQ, sK, rm, crit_idx, k_c, (const uint16_t *)Hq,
+        else attend_short_kernel<2, false><<<(unsigned)xcd_grid(total), 128, 0, st>>>(Q, K, (const uint16_t *)Vp, lvs, sQ, sK, rm, crit_idx, k_c, (const uint16_t *)Hq,
                                                                                       (const uint16_t *)WT, proj_per_head, phi, H, N, Nqb, Nkb, total, c_exp, (uint16_t *)O, O32);
         return hipGetLastError();
     }

@@ -12,8 +12,7 @@
 // The fp16 copy of V is exact: bf16 values are first divided by the power of two 2^e of the block's largest
 // magnitude (so that any bf16 tensor fits the range of fp16; entries more than 2^24 below the block's maximum
 // are the only ones to lose bits), E4M3 codes are taken as they are; the attention kernel gets e, or the base-2
-// logarithm of the E4M3 block scale, in `vks` and folds it into the exponent of its softmax weights; beside it the
-// largest norm of the block's K rows (e4m3: of the codes), with which that kernel bounds its exponents.
+// logarithm of the E4M3 block scale, in `lvs` and folds it into the exponent of its softmax weights.
 // The state and V^T tiles leave through LDS so that every store instruction writes 1 KB of whole rows.  The kernel is bound by
 // HBM (16 KB in, 16.6 KB out per block for bf16 inputs) where the launch is long, by the life of a block where it is not.
 // Seven blocks are in flight per CU (72 registers per lane; 64 for eight spilt, and cost a fifth).  Against one wave per block
@@ -142,11 +141,11 @@ template <bool FP8>
 __global__ __launch_bounds__(256, 7) void states_kernel(const void *__restrict__ K, const void *__restrict__ V,
                                                                   const float *__restrict__ sK, const float *__restrict__ sV,
                                                                   RowMap rm, int N, int Nkb,
-                                                                  uint16_t *__restrict__ hT, uint16_t *__restrict__ Vp, float2 *__restrict__ vks,
+                                                                  uint16_t *__restrict__ hT, uint16_t *__restrict__ Vp, float *__restrict__ lvs,
                                                                   double *__restrict__ kbar, int phi, unsigned state_wgs,
                                                                   const uint16_t *__restrict__ W, uint16_t *__restrict__ WT)
 {
-    asm volatile("" ::"s"(K), "s"(V), "s"(sK), "s"(sV), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(N), "s"(Nkb), "s"(hT), "s"(Vp), "s"(vks), "s"(kbar), "s"(phi), "s"(state_wgs), "s"(W), "s"(WT));      // all kernel arguments in one batch of scalar loads, here
+    asm volatile("" ::"s"(K), "s"(V), "s"(sK), "s"(sV), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(N), "s"(Nkb), "s"(hT), "s"(Vp), "s"(lvs), "s"(kbar), "s"(phi), "s"(state_wgs), "s"(W), "s"(WT));      // all kernel arguments in one batch of scalar loads, here
     if (blockIdx.x >= state_wgs) {     // workgroups past the states grid each lay out one projection matrix for the attention kernel
         const size_t m = (size_t)(blockIdx.x - state_wgs) * kD * kD;
         transpose_w_tile(W + m, WT + m, 256);
@@ -155,7 +154,6 @@ __global__ __launch_bounds__(256, 7) void states_kernel(const void *__restrict__
     __shared__ __attribute__((aligned(16))) uint16_t Ks[64 * kLdsRow];           // K rows, later phi^T [d][t], later the state
     __shared__ __attribute__((aligned(16))) uint16_t Vt[64 * kLdsRow];           // V^T [e][t]
     __shared__ uint32_t vmag[4];
-    __shared__ float knorms[2];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int l32 = lane & 31, g = lane >> 5;
     const long blk = blockIdx.x, bh = (long)(blockIdx.x / (unsigned)Nkb);
@@ -196,20 +194,14 @@ __global__ __launch_bounds__(256, 7) void states_kernel(const void *__restrict__
         // ---- phi: lane (l32, g) of wave 2, 3 owns channels 32 g .. of token row 32 (wave - 2) + l32; the other half row is
         // the lane's 32 positions away
         float x[32];
-        float kn[4];                                 // largest norm of the block's K rows, from above (rows past a ragged end
-                                                     // repeat the last one)
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const uint4 w = *(const uint4 *)(Ks + (32 * (wave - 2) + l32) * kLdsRow + 32 * g + c * 8);
-            kn[c] = dot2_bf16(w.x, w.x, dot2_bf16(w.y, w.y, dot2_bf16(w.z, w.z, dot2_bf16(w.w, w.w, 0.f))));
             x[c * 8 + 0] = bf16_lo(w.x); x[c * 8 + 1] = bf16_hi(w.x);
             x[c * 8 + 2] = bf16_lo(w.y); x[c * 8 + 3] = bf16_hi(w.y);
             x[c * 8 + 4] = bf16_lo(w.z); x[c * 8 + 5] = bf16_hi(w.z);
             x[c * 8 + 6] = bf16_lo(w.w); x[c * 8 + 7] = bf16_hi(w.w);
         }
-        const float ss = (kn[0] + kn[1]) + (kn[2] + kn[3]);
-        const float knorm = norm_from_above(wave_max_dpp(ss + xchg32(ss)));
-        if (lane == 0) knorms[wave - 2] = knorm;
         // phi = 0: softmax over the 64 channels; phi = 1: ELU(x)+1 elementwise (x+1 above 0, exp(x) below).
         // s is 1 for bf16 inputs and the K block scale for e4m3.
         const bool real = 32 * (wave - 2) + l32 < valid;         // rows past the sequence end contribute nothing
@@ -255,6 +247,7 @@ __global__ __launch_bounds__(256, 7) void states_kernel(const void *__restrict__
             const uint2 hi = bf16x4_to_f16x4(*(const uint2 *)(Vt + e * kLdsRow + src + 8), 127 - vexp);
             *(uint4 *)(vt + e * kBK + 8 * c) = make_uint4(lo.x, lo.y, hi.x, hi.y);
         }
+        if (lane == 0) lvs[blk] = FP8 ? __log2f(fmaxf(sV[blk], 1e-30f)) : (float)(vexp - 127);
     }
     lds_barrier();                                          // the rows are in registers and added: Ks may be overwritten
     if (wave >= 2) {
@@ -264,8 +257,7 @@ __global__ __launch_bounds__(256, 7) void states_kernel(const void *__restrict__
             col[(2 * d) * kLdsRow] = (uint16_t)(xp[d] & 0xFFFFu);
             col[(2 * d + 1) * kLdsRow] = (uint16_t)(xp[d] >> 16);
         }
-    } else if (wave == 1 && Vp != nullptr && lane == 0)
-        vks[blk] = make_float2(FP8 ? __log2f(fmaxf(sV[blk], 1e-30f)) : (float)(vexp - 127), fmaxf(knorms[0], knorms[1]));
+    }
     lds_barrier();
 
     // ---- h[d][e] = sum_t phi^T[d][t] * V^T[e][t]: wave w takes d = 32 (w / 2) .., e = 32 (w % 2) ..
@@ -309,14 +301,14 @@ __global__ __launch_bounds__(256, 7) void states_kernel(const void *__restrict__
 }
 
 hipError_t launch_states(const void *K, const void *V, const float *sK, const float *sV, bool fp8, RowMap rm,
-                         int BH, int N, void *hT, void *Vp, float2 *vks, double *kbar, int phi, const void *W, int nW, void *WT, hipStream_t st)
+                         int BH, int N, void *hT, void *Vp, float *lvs, double *kbar, int phi, const void *W, int nW, void *WT, hipStream_t st)
 {
     const int Nkb = (N + kBK - 1) / kBK;
     const long nblocks = (long)BH * Nkb;
     const unsigned grid = (unsigned)nblocks;
     const unsigned extra = W != nullptr ? (unsigned)nW : 0u;
-    if (fp8) states_kernel<true><<<grid + extra, 256, 0, st>>>(K, V, sK, sV, rm, N, Nkb, (uint16_t *)hT, (uint16_t *)Vp, vks, kbar, phi, grid, (const uint16_t *)W, (uint16_t *)WT);
-    else     states_kernel<false><<<grid + extra, 256, 0, st>>>(K, V, sK, sV, rm, N, Nkb, (uint16_t *)hT, (uint16_t *)Vp, vks, kbar, phi, grid, (const uint16_t *)W, (uint16_t *)WT);
+    if (fp8) states_kernel<true><<<grid + extra, 256, 0, st>>>(K, V, sK, sV, rm, N, Nkb, (uint16_t *)hT, (uint16_t *)Vp, lvs, kbar, phi, grid, (const uint16_t *)W, (uint16_t *)WT);
+    else     states_kernel<false><<<grid + extra, 256, 0, st>>>(K, V, sK, sV, rm, N, Nkb, (uint16_t *)hT, (uint16_t *)Vp, lvs, kbar, phi, grid, (const uint16_t *)W, (uint16_t *)WT);
     return hipGetLastError();
 }
 

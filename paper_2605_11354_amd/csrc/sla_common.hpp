@@ -69,10 +69,6 @@ __device__ __forceinline__ float bf16_round(float x) { return (float)(__bf16)x; 
 // exp2 on the hardware transcendental unit (v_exp_f32); exp2(-inf) = 0
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// 2-norm from a sum of squares, rounded up past the rounding of the sum (64 terms in fp32), and with a floor where squares
-// may have underflowed: an upper bound
-__device__ __forceinline__ float norm_from_above(float ss) { return fmaf(__builtin_amdgcn_sqrtf(ss), 1.001f, 1.7347235e-18f); }
-
 // value held by the lane 32 positions away (lanes l and l^32 exchange)
 __device__ __forceinline__ float xchg32(float v) { return __shfl_xor(v, 32, 64); }
 

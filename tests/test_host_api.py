@@ -116,3 +116,17 @@ def test_fp8_linear_and_quantiser_validate_on_the_host(lib):
     rc = lib.sla_quantise_e4m3(C.c_void_p(16), C.c_int32(1), C.c_int32(2), C.c_int32(640), C.c_int32(64), C.c_int32(7), C.c_void_p(16), C.c_void_p(16), null)
     assert rc == B.SLA_ERR_INVALID_ARG
     assert lib.sla_quantise_e4m3(null, C.c_int32(0), C.c_int32(2), C.c_int32(640), C.c_int32(64), C.c_int32(0), null, null, null) == B.SLA_OK
+
+
+# forwards that fill the library's own workspace (96 MiB) to within a few kilobytes: they fit
+@pytest.mark.parametrize("H,N,bq", [(8, 25280, 64), (1, 178560, 128)])
+def test_workspace_at_the_limit_of_the_static_one(lib, H, N, bq):
+    p = B.make_params(1, H, N, bq, 64, 0.05, 0.8)
+    k_c, _ = B.sla_resolve_counts(p)
+    nqb, nkb, up = -(-N // bq), -(-N // 64), lambda x, a: -(-x // a) * a
+    groups = max(1, min(-(-2048 // (4 * H)), -(-(-(-N // 32)) // 4)))
+    parts = [nqb * 64 * 8, nkb * 64 * 8, nqb * up(nkb, 8) * 8, nqb * up(nkb, 64) // 8, nqb * k_c * 4,      # means, logits, masks, lists
+             nkb * 65 * 64 * 2, nqb * 65 * 64 * 2, 64 * 64 * 2 / H, nkb * 64 * 64 * 2, nkb * 4,             # states, sums, W^T, V^T, its scales
+             groups * 64 * 64 * 4]                                                                         # partials of the gradient
+    assert B.sla_workspace_bytes(p) == sum(up(int(H * x), 256) for x in parts)
+    assert 0 <= 96 * 1024 * 1024 - B.sla_workspace_bytes(p) < 64 * 1024
