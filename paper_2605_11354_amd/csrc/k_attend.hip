@@ -135,6 +135,21 @@ __device__ __forceinline__ float max16(const f32x16 &s)
     return max3(max3(a, b, c), max3(d, e, s[15]), a);
 }
 
+// The same, NaN if one of them is (v_maximum3_f32), and over the lane pair that shares the row
+__device__ __forceinline__ float max3_nan(float a, float b, float c) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c); }
+__device__ __forceinline__ float max16_nan(const f32x16 &s)
+{
+    const float a = max3_nan(s[0], s[1], s[2]), b = max3_nan(s[3], s[4], s[5]), c = max3_nan(s[6], s[7], s[8]);
+    const float d = max3_nan(s[9], s[10], s[11]), e = max3_nan(s[12], s[13], s[14]);
+    return max3_nan(max3_nan(a, b, c), max3_nan(d, e, s[15]), a);
+}
+__device__ __forceinline__ float pair_max_nan(float v)
+{
+    const uint32_t u = __float_as_uint(v);
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __builtin_elementwise_maximum(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 template <int NWAVES, bool FP8, int NSLOTS = 3>
 struct Tile {
     static constexpr int KBYTES = FP8 ? 64 * 64 : 64 * 128;     // K tile (e4m3 / bf16)
@@ -303,8 +318,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     for (int x = 0; x < 16; ++x) zero16[x] = 0.f;
     f32x16 oacc[2] = {zero16, zero16};
     // Running state of the lane's row.  m_run: reference exponent (log2 domain) of the weights; lsum: the row sum,
-    // accumulated from the fp16 weights the second product consumes (divided by the V scale ratio again); l_full: row sums formed in fp32 by the careful steps (already complete over the lane pair).
-    float m_run = -INFINITY, l_full = 0.f;
+    // accumulated from the fp16 weights the second product consumes (divided by the V scale ratio again); l_full: row sums
+    // formed in fp32 by the careful steps (already complete over the lane pair), and NaN for a spoilt row (see softmax_careful).
+    float m_run = -3.4028235e38f, l_full = 0.f;        // (finite from the start: its difference to a masked key is -inf, not NaN)
     // The row sums of the fast steps come from the matrix unit: A holds 1 / (V scale ratio) where row i = lane % 16 and the
     // 8-weight chunk lane / 16 of K belong together -- i % 4 == 0 and (i / 4) % 2 == chunk % 2 -- and 0 elsewhere, so that
     // row 0 (8) adds the chunks of queries 0..15 and row 4 (12) those of queries 16..31 of the P operand, and register 0 of
@@ -501,23 +517,32 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     };
     // Careful form (first unit of a row, ragged or tiny-scale tiles): exact maximum of the unit, row sums in fp32
     // from weights that do not carry the V scale.
+    // A row with a NaN or +inf among its logits (infinities or NaN in its Q, or in K) comes out NaN, and must not touch the
+    // others: the row sums of the fast steps tell rows q and q + 16 apart by zeros in A, and 0 NaN = NaN.  So its weights are
+    // replaced by zeros, here and in front of a fast step (raise_reference), and its sum remembers.
     auto softmax_careful = [&](f32x16 &s, const TileInfo &t, Weights &w) __attribute__((always_inline)) {
-        const float top = pair_max(max16(s)) * t.cj + t.lsv;        // -inf if the lane's row sees no real key in this unit
+        const float top = pair_max_nan(max16_nan(s)) * t.cj + t.lsv;        // -inf if the lane's row sees no real key in this unit
         if (__ballot(top > m_run)) {
-            const float m_new = fmaxf(m_run, top);
+            const float m_new = top < INFINITY ? fmaxf(m_run, top) : m_run;
             rescale(m_new == m_run ? 1.0f : fast_exp2(m_run - m_new));
             m_run = m_new;
         }
-        const float mfin = m_run == -INFINITY ? 0.f : m_run;
         const float r = fast_exp2(t.lsv);
         float sum = 0.f;
 #pragma unroll
         for (int x = 0; x < 16; ++x) {
-            const float pu = fast_exp2(fmaf(s[x], t.cj, -mfin));   // weight without the V scale: what the row sum adds up
+            const float pu = fast_exp2(fmaf(s[x], t.cj, -m_run));  // weight without the V scale: what the row sum adds up
             sum += pu;
             s[x] = pu * r;                                          // weight with it: what multiplies the scaled V^T
         }
-        l_full += sum + xchg32(sum);
+        sum += xchg32(sum);
+        const bool spoilt = !(sum < INFINITY);
+        if (__ballot(spoilt)) {
+#pragma unroll
+            for (int x = 0; x < 16; ++x) s[x] = spoilt ? 0.f : s[x];
+            sum = spoilt ? __builtin_nanf("") : sum;
+        }
+        l_full += sum;
         w.p[0] = pack8_f16(s, 0);
         w.p[1] = pack8_f16(s, 8);
         w.inv2 = 0u;
@@ -563,9 +588,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
 #define SLA_SB() __builtin_amdgcn_sched_barrier(0)
 #define SLA_PIN(...) asm volatile("" : __VA_ARGS__)
     // Whether some lane's largest exponent in the unit whose S^T is s would exceed kRaise against the lane's running
-    // maximum (stale by that much, or still -inf): such a unit takes the careful step, which raises the maximum exactly.
+    // maximum (stale by that much, or not set yet), or is NaN: such a unit takes the careful step, which raises the maximum exactly.
     auto overflows = [&](const f32x16 &s, const TileInfo &t) __attribute__((always_inline)) {
-        return __ballot(!(fmaf(max16(s), t.cj, t.lsv - m_run) <= kRaise)) != 0;
+        return __ballot(!(fmaf(max16_nan(s), t.cj, t.lsv - m_run) <= kRaise)) != 0;
     };
     bool over_cur = true;                              // the first unit is careful anyway
 
@@ -687,7 +712,14 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     // the overflow checks could be left out, small weights lost bits, and every move of the window raised it again.  Keeping the
     // checks costs nothing: a layer of 16 heads x 43968 tokens 656 us with and 658 without them, 10992 tokens 98 and 99.)
     auto raise_reference = [&](const TileInfo &t) __attribute__((always_inline)) {
-        const float m_new = fmaxf(m_run, pair_max(max16(s_cur)) * t.cj + t.lsv);
+        const float top = pair_max_nan(max16_nan(s_cur)) * t.cj + t.lsv;
+        const bool spoilt = !(top < INFINITY);
+        if (__ballot(spoilt)) {
+#pragma unroll
+            for (int x = 0; x < 16; ++x) s_cur[x] = spoilt ? -INFINITY : s_cur[x];
+            l_full = spoilt ? __builtin_nanf("") : l_full;
+        }
+        const float m_new = spoilt ? m_run : fmaxf(m_run, top);
         const float alpha = m_new == m_run ? 1.0f : fast_exp2(m_run - m_new);
         rescale(alpha);
         const _Float16 ah = (_Float16)alpha;
@@ -805,7 +837,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     uint8_t *stA = lds + kHqOff, *stB = lds + kWtOff;
     const uint8_t *zrow = lds + T::ZOFF;
     // ---- normalise the sparse output: the weights carried the V scale relative to the first tile's
-    const float inv_l = l_run > 0.f ? fast_exp2(lv_ref) / l_run : 0.f;
+    const float inv_l = l_run > 0.f ? fast_exp2(lv_ref) / l_run : l_run;     // 0 for an empty list, NaN for a spoilt row
 #pragma unroll
     for (int e = 0; e < 2; ++e)
 #pragma unroll
