@@ -64,9 +64,9 @@ constexpr float kLog2e = 1.4426950408889634f;
 // A lane raises the running maximum of its row when a weight of the current unit would exceed 2^kRaise times
 // the largest weight seen when the maximum was last set; fp16 holds 2^kRaise with room to spare (max 65504).
 constexpr float kRaise = 12.0f;
-// A key block whose V scale differs from that of the row's first block by more than 2^kTinyV either way takes the
-// careful step: its weights (or the factor that divides the scale out of the row sums again) would leave the range
-// of fp16, so its row sums are formed in fp32.
+// A key block whose V scale differs from that of the row's first block by more than 2^kTinyV either way, or is as far below
+// the largest one of the list so far, takes the careful step: its weights (or the factor that divides the scale out of the row
+// sums again) would leave the range of fp16, so its row sums are formed in fp32.
 constexpr float kTinyV = 8.0f;
 
 typedef __attribute__((address_space(3))) void *lds_void_p;
@@ -341,7 +341,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     float d_lv = 0.f, d_cj = 0.f, lv_ref = 0.f;
     // One bit per window entry: set if its tile needs the guarded form of an iteration (past the end of the list,
     // the ragged last block, a V scale far from the first tile's).
-    unsigned long long d_bad = ~0ull;
+    unsigned long long d_bad = ~0ull, d_far = 0;         // (d_far: the last of these alone)
+    float lv_top = -INFINITY;                            // largest V scale of the windows so far
     // k: number of leading valid entries of the list (a list taken from given labels may end in -1 entries)
     int k = 0;
     {
@@ -372,7 +373,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
         // log2 of the V scale of the first tile: the reference of the weights
         if (first) lv_ref = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(lv)));
         d_lv = lv - lv_ref;
-        d_bad = __ballot(wbase + lane >= k || d_j == ragged_j || !(fabsf(d_lv) <= kTinyV));
+        lv_top = fmaxf(lv_top, wave_max_dpp(wbase + lane < k ? d_lv : -INFINITY));
+        d_far = __ballot(!(fabsf(d_lv) <= kTinyV) || d_lv < lv_top - kTinyV);
+        d_bad = d_far | __ballot(wbase + lane >= k || d_j == ragged_j);
     };
     auto load_window = [&](int wb) __attribute__((always_inline)) {
         const int idx = wb + lane;
@@ -435,7 +438,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
         t.valid = entry_j(c) == ragged_j ? tail_rows : kBK;
         t.cj = FP8 ? __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(d_cj), c - wbase)) : c_exp;
         t.lsv = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(d_lv), c - wbase));   // the V scale of the tile rides on the weights: P' = P * 2^lsv
-        t.tiny = fabsf(t.lsv) > kTinyV;
+        t.tiny = (d_far >> (c - wbase)) & 1;
         t.inv2 = inv2_of(t.lsv);                       // and is divided out of the row sums again
         return t;
     };

@@ -90,3 +90,20 @@ def test_keys_that_grow_along_the_list(oracle, bq, dtype):
     err = _error(case, oracle, lab, [(0, 0), (0, case.Nqb - 1)])
     print(f"bq={bq} {dtype}: {err:.3e}")
     assert err <= 2e-3                                   # fp16 weights (2^-11) on a sum that cancels nothing
+
+
+@pytest.mark.parametrize("bq,dtype", [(64, "bf16"), (128, "bf16"), (64, "fp8"), (128, "fp8")])
+@pytest.mark.parametrize("scales", [(-17, 0), (-12, 0), (0, -12), (0, 12, 0, -5, 6)])
+def test_values_of_far_apart_scales(oracle, bq, dtype, scales):
+    """Values of 2^scales[i % ...] in block i: a block of small values counts in the sums whatever stands in front of it."""
+    rng = np.random.default_rng(len(scales))
+    nkb = 72
+    q, k, v = (rng.standard_normal((nkb * 64 - 5, 64)) for _ in range(3))
+    v *= 2.0 ** np.array(scales, float)[np.arange(len(v)) // 64 % len(scales), None]
+    case = _case(q, k, v, bq, dtype)
+    lab = np.full((1, 1, case.Nqb, case.Nkb), 2, np.int8)
+    lab[0, 0, 0, 9:] = 0                                    # a short list and the whole of it
+    case.p.k_crit = nkb
+    err = max(_error(case, oracle, lab, [(0, 0)]), _error(case, oracle, lab, [(0, case.Nqb - 1)]))
+    print(f"bq={bq} {dtype} {scales}: {err:.3e}")
+    assert err <= 2.0 ** -8
