@@ -166,6 +166,17 @@ struct Tile {
     static constexpr int LDS = WOFF + (FP8 ? 8192 : 0);
 };
 
+// log2 of the V scale of a lane's list entry relative to the list's reference, which is that of the first entry that has one
+// (first: set it from this window).  A block of zeros (lv = -inf) fits any scale and takes the reference.
+__device__ __forceinline__ float relative_scale(float lv, bool in, bool first, float &lv_ref)
+{
+    if (first) {
+        const unsigned long long m = __ballot(in && lv != -INFINITY);
+        lv_ref = m ? __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(lv), __builtin_ctzll(m))) : 0.f;
+    }
+    return lv == -INFINITY ? 0.f : lv - lv_ref;
+}
+
 // The lane index, computed here (two instructions) and not carried in a register from the top of the kernel
 __device__ __forceinline__ int lane_now()
 {
@@ -370,9 +381,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
         // exp2 constant of the tile: softmax scale * log2(e) (* Q and K block scales for e4m3)
         d_cj = FP8 ? fmaxf(c_exp * qscale * sK[bh * Nkb + d_j], 1e-30f) : c_exp;
         asm volatile("" : "+v"(lv), "+v"(d_cj));       // the loads complete here, not at some later first use
-        // log2 of the V scale of the first tile: the reference of the weights
-        if (first) lv_ref = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(lv)));
-        d_lv = lv - lv_ref;
+        d_lv = relative_scale(lv, wbase + lane < k, first, lv_ref);
         lv_top = fmaxf(lv_top, wave_max_dpp(wbase + lane < k ? d_lv : -INFINITY));
         d_far = __ballot(!(fabsf(d_lv) <= kTinyV) || d_lv < lv_top - kTinyV);
         d_bad = d_far | __ballot(wbase + lane >= k || d_j == ragged_j);
@@ -1064,11 +1073,11 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
     int k = okm == ~0ull ? 64 : __builtin_ctzll(~okm);
     k = __builtin_amdgcn_readfirstlane(min(k, k_c));
     const int d_j = jok ? j0 : 0;
-    float d_lv = lvs[bh * Nkb + d_j];
+    float lv = lvs[bh * Nkb + d_j];
     float d_cj = FP8 ? fmaxf(c_exp * qscale * sK[bh * Nkb + d_j], 1e-30f) : c_exp;
-    asm volatile("" : "+v"(d_lv), "+v"(d_cj));
-    const float lv_ref = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(d_lv)));
-    d_lv -= lv_ref;
+    asm volatile("" : "+v"(lv), "+v"(d_cj));
+    float lv_ref = 0.f;
+    const float d_lv = relative_scale(lv, lane < k, true, lv_ref);
     __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));      // vmcnt(0): Q, the list and the operands have landed
     wait_copies_and_barrier<0>();
 

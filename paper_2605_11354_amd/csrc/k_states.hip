@@ -12,7 +12,8 @@
 // The fp16 copy of V is exact: bf16 values are first divided by the power of two 2^e of the block's largest
 // magnitude (so that any bf16 tensor fits the range of fp16; entries more than 2^24 below the block's maximum
 // are the only ones to lose bits), E4M3 codes are taken as they are; the attention kernel gets e, or the base-2
-// logarithm of the E4M3 block scale, in `lvs` and folds it into the exponent of its softmax weights.
+// logarithm of the E4M3 block scale, in `lvs` and folds it into the exponent of its softmax weights (-inf for a block of zeros,
+// which has no scale of its own).
 // The state and V^T tiles leave through LDS so that every store instruction writes 1 KB of whole rows.  The kernel is bound by
 // HBM (16 KB in, 16.6 KB out per block for bf16 inputs) where the launch is long, by the life of a block where it is not.
 // Seven blocks are in flight per CU (72 registers per lane; 64 for eight spilt, and cost a fifth).  Against one wave per block
@@ -162,14 +163,14 @@ __global__ __launch_bounds__(256, 7) void states_kernel(const void *__restrict__
         BlockRegs<FP8> regs;
         load_block<FP8>(regs, K, V, rm.head(bh) + (size_t)t0 * rm.ts, rm.ts, valid, tid);
         stage_block<FP8>(regs, Ks, Vt, tid);
-        if constexpr (!FP8) {
-            const uint32_t mx = wave_max_magnitude(regs.v);
-            if (lane == 0) vmag[wave] = mx;
-        }
+        uint32_t mx;
+        if constexpr (FP8) mx = __ballot(((regs.v[0] | regs.v[1] | regs.v[2] | regs.v[3]) & 0x7F7F7F7Fu) != 0u) != 0ull;   // zero or not is all there is to know
+        else mx = wave_max_magnitude(regs.v);
+        if (lane == 0) vmag[wave] = mx;
     }
     lds_barrier();
-    int vexp = 127;                              // bf16: exponent field (1..254) of the block's largest |V| (127 = 2^0)
-    if constexpr (!FP8) vexp = min(max((int)(max(max(vmag[0], vmag[1]), max(vmag[2], vmag[3])) >> 7), 1), 254);
+    const uint32_t vmax = max(max(vmag[0], vmag[1]), max(vmag[2], vmag[3]));     // bits of the block's largest |V| (e4m3: 0 or 1)
+    const int vexp = FP8 ? 127 : min(max((int)(vmax >> 7), 1), 254);             // its exponent field (127 = 2^0)
 
     uint32_t xp[16];                             // phi of the lane's half row, bf16 pairs
     if (wave == 0) {
@@ -247,7 +248,7 @@ __global__ __launch_bounds__(256, 7) void states_kernel(const void *__restrict__
             const uint2 hi = bf16x4_to_f16x4(*(const uint2 *)(Vt + e * kLdsRow + src + 8), 127 - vexp);
             *(uint4 *)(vt + e * kBK + 8 * c) = make_uint4(lo.x, lo.y, hi.x, hi.y);
         }
-        if (lane == 0) lvs[blk] = FP8 ? __log2f(fmaxf(sV[blk], 1e-30f)) : (float)(vexp - 127);
+        if (lane == 0) lvs[blk] = vmax == 0u ? -INFINITY : FP8 ? __log2f(fmaxf(sV[blk], 1e-30f)) : (float)(vexp - 127);
     }
     lds_barrier();                                          // the rows are in registers and added: Ks may be overwritten
     if (wave >= 2) {

@@ -46,7 +46,7 @@ hipError_t launch_labels_prepare(const int8_t *lab_dense, long rows, int Nkb, in
 // per-key-block states: hT [BH,Nkb,65,64] bf16; optionally also Vp [BH,Nkb,64,64] fp16, the transposed,
 // key-permuted V tiles the attention kernel reads (bf16 V divided by a power of two per block, E4M3 codes
 // unscaled) with lvs [BH,Nkb] fp32, the base-2 logarithm of what one unit of Vp stands for (that power of two,
-// or the E4M3 block scale), and kbar [BH,Nkb,64] fp64, the block means of K (same arithmetic as launch_pool);
+// -inf for a block of zeros, or the E4M3 block scale), and kbar [BH,Nkb,64] fp64, the block means of K (same arithmetic as launch_pool);
 // NULL skips Vp + lvs, or kbar.  With W != NULL the launch also does the work of launch_transpose_w(W, nW, WT)
 // in nW extra workgroups.
 hipError_t launch_states(const void *K, const void *V, const float *sK, const float *sV, bool fp8, RowMap rm,

@@ -92,6 +92,29 @@ def test_keys_that_grow_along_the_list(oracle, bq, dtype):
     assert err <= 2e-3                                   # fp16 weights (2^-11) on a sum that cancels nothing
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("bq", [64, 128])
+@pytest.mark.parametrize("length,zeros", [(2, [0]), (2, [0, 1]), (5, [0]), (5, [2, 4]), (9, [0, 1, 2, 8]), (70, list(range(66)))])
+def test_blocks_of_zero_values(oracle, bq, dtype, length, zeros):
+    """Key blocks whose V is zero weigh like any other, also at the head of a list (positions `zeros` of the list)."""
+    rng = np.random.default_rng(length)
+    nkb = 72
+    q, k, v = (rng.standard_normal((nkb * 64 - 5, 64)) for _ in range(3))
+    js = np.sort(rng.choice(nkb - 1, length, replace=False))
+    for z in zeros:
+        v[64 * js[z]:64 * js[z] + 64] = 0.0
+    case = _case(q, k, v, bq, dtype)
+    case.p.k_crit, case.p.k_neg = length, 0
+    lab = np.zeros((1, 1, case.Nqb, case.Nkb), np.int8)
+    lab[..., js] = 2
+    sel = [(0, 0), (0, case.Nqb - 1)]
+    ref = case.oracle_attend(oracle, lab, sel=sel, want_parts=True)["O_sparse"]
+    got = G.gather_blocks(_sparse_f32(case, lab), sel, bq, 1)
+    err = np.abs(got - ref).max() / max(np.sqrt(np.mean(ref ** 2)), 1e-3)
+    print(f"bq={bq} {dtype} {length} {zeros[-1]}: {err:.3e}")
+    assert err <= 2.0 ** -8                                 # fp16 weights, 2^-11, on sums whose terms cancel to a few times that
+
+
 @pytest.mark.parametrize("bq,dtype", [(64, "bf16"), (128, "bf16"), (64, "fp8"), (128, "fp8")])
 @pytest.mark.parametrize("scales", [(-17, 0), (-12, 0), (0, -12), (0, 12, 0, -5, 6)])
 def test_values_of_far_apart_scales(oracle, bq, dtype, scales):
