@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void quantise_rows_kernel(RowsIn ma, RowsIn mb
     const float scale = fmaxf(fmaxf(fmaxf(red[0][r0], red[1][r0]), fmaxf(red[2][r0], red[3][r0])), 1e-8f) / 448.0f;
     if (wave == 0 && c == 0 && row < R) m.scales[32 * grp + row] = scale;
     uint8_t *const out = m.codes + 32 * grp * cols + (((c & 1) * 2 + (c >> 1)) * R + row) * 16;
-    const BlockDivisor divide(scale, true);
+    const BlockDivisor divide(scale);
     for (int p = 0; p < passes; ++p) {
         if (!ONE) load(p);
 #pragma unroll

@@ -38,7 +38,7 @@ __global__ __launch_bounds__(256) void quantise_e4m3_kernel(const uint16_t *__re
     const float scale = fmaxf(amax, 1e-8f) / 448.0f;
     if (lane == 0) scales[blk] = scale;
     uint8_t *out = codes + rm.head(bh) + (size_t)t0 * rm.ts + (lane & 7) * 8;
-    const BlockDivisor divide(scale, true);
+    const BlockDivisor divide(scale);
 #pragma unroll
     for (int k = 0; k < kPieces; ++k) {
         const int r = (lane >> 3) + 8 * k;

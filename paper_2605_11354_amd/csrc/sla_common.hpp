@@ -124,11 +124,10 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16 &a, int base)
 // most 448 in magnitude and anything below 2^-10 becomes the code 0, so the exponent range plays no part for a finite scale.
 // Three instructions per element instead of the ten of the division's expansion.
 // An infinite scale: x / inf is a zero of x's sign, and NaN for an infinite x.  d = 0 and y = 0 give just that
-// (q = x 0, RN(q + x 0)); the qkv epilogue does not ask for it (NaN for every x: the code of -448).
+// (q = x 0, RN(q + x 0)).
 struct BlockDivisor {
     float d, y;
-    __device__ __forceinline__ explicit BlockDivisor(float scale, bool infinite = false)
-        : d(infinite && scale == __builtin_inff() ? 0.f : scale), y(1.0f / scale) {}
+    __device__ __forceinline__ explicit BlockDivisor(float scale) : d(scale == __builtin_inff() ? 0.f : scale), y(1.0f / scale) {}
     __device__ __forceinline__ float operator()(float x) const
     {
         const float q = x * y;

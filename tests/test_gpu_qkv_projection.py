@@ -111,6 +111,30 @@ def test_forward_on_the_fused_projection_output():
     assert torch.isfinite(outs[0][0].float()).all()
 
 
+@pytest.mark.parametrize("N,H,d_in", [(333, 3, 128), (11100, 16, 128)])      # 128-token and 256-token tiles
+def test_fused_epilogue_on_overflow_and_nan(N, H, d_in):
+    """Blocks of y with infinities and NaN (an infinite or NaN entry of x or of the bias): still the unfused call's bytes, that
+    is zeros of their sign for the finite values of a block whose scale is infinite."""
+    from paper_2605_11354_amd import binding as B
+    xb, Wb, bb = _inputs(1, N, H, d_in, 51)
+    xb[70, 3], xb[200, 9] = 0x7F80, 0x7FC0                              # +inf, NaN: their whole rows of y
+    bb[5], bb[64 * H + 7], bb[2 * 64 * H + 64] = 0xFF80, 0x7F80, 0x7FC0  # -inf, +inf, NaN: a channel of q, of k and of v in every block
+    codes, scales = _fused(1, N, H, 128, xb, Wb, bb)
+    y = torch.empty((N, 3 * H * 64), dtype=torch.bfloat16, device="cuda")
+    B.sla_fp8_linear(G.dev_bf16(xb), G.dev_bf16(Wb), G.dev_bf16(bb), y)
+    y = y.view(1, N, 3, H, 64)
+    infinite = 0
+    for w, blk in enumerate((128, 64, 64)):
+        c = torch.empty((1, N, H, 64), dtype=torch.uint8, device="cuda")
+        s = torch.empty((1, H, -(-N // blk)), dtype=torch.float32, device="cuda")
+        B.sla_quantise_e4m3(y[:, :, w].contiguous(), blk, c, s, layout="bnhd")
+        torch.cuda.synchronize()
+        infinite += int(torch.isinf(s).sum())
+        assert torch.equal(s, scales[w]), ("scales", w)
+        assert torch.equal(c, codes[w]), ("codes", w, (c != codes[w]).nonzero()[:4])
+    assert infinite > 2 * (N // 128)
+
+
 def test_unsupported_shapes_are_refused():
     from paper_2605_11354_amd import binding as B
     xb, Wb, bb = _inputs(2, 300, 2, 128, 49)
