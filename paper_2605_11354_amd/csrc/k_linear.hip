@@ -310,7 +310,8 @@ __global__ __launch_bounds__(256, 2) void fp8_gemm_kernel(const uint8_t *__restr
     SLA_GT(2);
 
     // Accumulator (a,b) register 4q+r of lane (l32, g): channel o0 + wo + 32a + 8q + 4g + r, token i0 + wi + 32b + l32.
-    // y = (acc * s_token) * s_channel + bias, two roundings before the bf16 one.  No staging in LDS: lanes l and l + 32 hold
+    // y = acc * (s_token * s_channel) + bias, two roundings before the bf16 one (the scales first: acc times one of them alone can
+    // overflow where y does not).  No staging in LDS: lanes l and l + 32 hold
     // the other half of each other's channels, and v_permlane32_swap brings the pieces of a 16-byte store together.
     float4 sw4[2][4], bi4[2][4];
     float si[TB];
@@ -325,10 +326,10 @@ __global__ __launch_bounds__(256, 2) void fp8_gemm_kernel(const uint8_t *__restr
 #pragma unroll
     for (int b = 0; b < TB; ++b) si[b] = ts[wi + 32 * b + l32];
     auto value = [&](int a, int b, int q, float (&v)[4]) {
-        v[0] = fmaf(acc[a][b][4 * q + 0] * si[b], sw4[a][q].x, bi4[a][q].x);
-        v[1] = fmaf(acc[a][b][4 * q + 1] * si[b], sw4[a][q].y, bi4[a][q].y);
-        v[2] = fmaf(acc[a][b][4 * q + 2] * si[b], sw4[a][q].z, bi4[a][q].z);
-        v[3] = fmaf(acc[a][b][4 * q + 3] * si[b], sw4[a][q].w, bi4[a][q].w);
+        v[0] = fmaf(acc[a][b][4 * q + 0], si[b] * sw4[a][q].x, bi4[a][q].x);
+        v[1] = fmaf(acc[a][b][4 * q + 1], si[b] * sw4[a][q].y, bi4[a][q].y);
+        v[2] = fmaf(acc[a][b][4 * q + 2], si[b] * sw4[a][q].z, bi4[a][q].z);
+        v[3] = fmaf(acc[a][b][4 * q + 3], si[b] * sw4[a][q].w, bi4[a][q].w);
     };
     auto swap32 = [](uint32_t &lo, uint32_t &hi) {                               // upper lanes of lo <-> lower lanes of hi
         const auto r = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);

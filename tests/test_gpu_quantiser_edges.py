@@ -56,3 +56,19 @@ def test_codes_of_infinities_and_nan():
     q = np.clip(xf[1:] / s[1:, None, None], np.float32(-448), np.float32(448))
     q = torch.from_numpy(np.where(np.isnan(q), np.float32(-448), q)).to(torch.float8_e4m3fn).view(torch.uint8).numpy()
     assert np.array_equal(c[1:], q)
+
+
+@pytest.mark.parametrize("N,d_in,d_out", [(40, 256, 72), (4100, 256, 2048), (8200, 384, 2048)])     # the three token tiles
+@pytest.mark.parametrize("size_x,size_W", [(1e36, 1e-6), (1e-6, 1e36)])
+def test_layer_on_very_large_operands(oracle, N, d_in, d_out, size_x, size_W):
+    """The scale of one operand alone is far outside the range of y: no step on the way to a finite y overflows."""
+    rng = np.random.default_rng(N)
+    bits = lambda a: (np.ascontiguousarray(a, np.float32).view(np.uint32) >> 16).astype(np.uint16)       # (truncated: nothing flushed)
+    xb, Wb = bits(rng.standard_normal((N, d_in)) * size_x), bits(rng.standard_normal((d_out, d_in)) * size_W)
+    y = torch.full((N, d_out), float("nan"), dtype=torch.bfloat16, device="cuda")
+    B.sla_fp8_linear(G.dev_bf16(xb), G.dev_bf16(Wb), None, y)
+    torch.cuda.synchronize()
+    ref, got = oracle.fp8_linear(xb, Wb, None), G.bf16_tensor_to_f64(y)
+    rms = float(np.sqrt(np.mean(ref ** 2)))
+    excess = np.maximum(np.abs(got - ref) - G.bf16_half_ulp(ref), 0.0).max() / rms
+    assert excess <= max(1e-3, (d_in + 3) * 2.0 ** -24 * np.sqrt(d_in)), excess
