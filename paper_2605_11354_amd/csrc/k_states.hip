@@ -143,10 +143,10 @@ __global__ __launch_bounds__(256, 7) void states_kernel(const void *__restrict__
                                                                   const float *__restrict__ sK, const float *__restrict__ sV,
                                                                   RowMap rm, int N, int Nkb,
                                                                   uint16_t *__restrict__ hT, uint16_t *__restrict__ Vp, float *__restrict__ lvs,
-                                                                  double *__restrict__ kbar, int phi, unsigned state_wgs,
+                                                                  double *__restrict__ kbar, int phi, unsigned first, unsigned state_wgs,
                                                                   const uint16_t *__restrict__ W, uint16_t *__restrict__ WT)
 {
-    asm volatile("" ::"s"(K), "s"(V), "s"(sK), "s"(sV), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(N), "s"(Nkb), "s"(hT), "s"(Vp), "s"(lvs), "s"(kbar), "s"(phi), "s"(state_wgs), "s"(W), "s"(WT));      // all kernel arguments in one batch of scalar loads, here
+    asm volatile("" ::"s"(K), "s"(V), "s"(sK), "s"(sV), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(N), "s"(Nkb), "s"(hT), "s"(Vp), "s"(lvs), "s"(kbar), "s"(phi), "s"(first), "s"(state_wgs), "s"(W), "s"(WT));      // all kernel arguments in one batch of scalar loads, here
     if (blockIdx.x >= state_wgs) {     // workgroups past the states grid each lay out one projection matrix for the attention kernel
         const size_t m = (size_t)(blockIdx.x - state_wgs) * kD * kD;
         transpose_w_tile(W + m, WT + m, 256);
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256, 7) void states_kernel(const void *__restrict__
     __shared__ uint32_t vmag[4];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int l32 = lane & 31, g = lane >> 5;
-    const long blk = blockIdx.x, bh = (long)(blockIdx.x / (unsigned)Nkb);
+    const long blk = first + blockIdx.x, bh = (long)((unsigned)blk / (unsigned)Nkb);
     const int t0 = (int)(blk - bh * Nkb) * kBK, valid = min(kBK, N - t0);
     {
         BlockRegs<FP8> regs;
@@ -306,10 +306,14 @@ hipError_t launch_states(const void *K, const void *V, const float *sK, const fl
 {
     const int Nkb = (N + kBK - 1) / kBK;
     const long nblocks = (long)BH * Nkb;
-    const unsigned grid = (unsigned)nblocks;
-    const unsigned extra = W != nullptr ? (unsigned)nW : 0u;
-    if (fp8) states_kernel<true><<<grid + extra, 256, 0, st>>>(K, V, sK, sV, rm, N, Nkb, (uint16_t *)hT, (uint16_t *)Vp, lvs, kbar, phi, grid, (const uint16_t *)W, (uint16_t *)WT);
-    else     states_kernel<false><<<grid + extra, 256, 0, st>>>(K, V, sK, sV, rm, N, Nkb, (uint16_t *)hT, (uint16_t *)Vp, lvs, kbar, phi, grid, (const uint16_t *)W, (uint16_t *)WT);
+    // a launch takes at most 2^20 blocks (a grid is limited to 2^32 threads; 2^20 blocks are some 6 ms); the last one lays out W
+    constexpr long kMost = 1l << 20;
+    for (long first = 0; first < nblocks; first += kMost) {
+        const bool last = nblocks - first <= kMost;
+        const unsigned grid = (unsigned)(last ? nblocks - first : kMost), extra = last && W != nullptr ? (unsigned)nW : 0u;
+        if (fp8) states_kernel<true><<<grid + extra, 256, 0, st>>>(K, V, sK, sV, rm, N, Nkb, (uint16_t *)hT, (uint16_t *)Vp, lvs, kbar, phi, (unsigned)first, grid, (const uint16_t *)W, (uint16_t *)WT);
+        else     states_kernel<false><<<grid + extra, 256, 0, st>>>(K, V, sK, sV, rm, N, Nkb, (uint16_t *)hT, (uint16_t *)Vp, lvs, kbar, phi, (unsigned)first, grid, (const uint16_t *)W, (uint16_t *)WT);
+    }
     return hipGetLastError();
 }
 
