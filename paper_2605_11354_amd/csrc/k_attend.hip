@@ -29,7 +29,7 @@
 // runs O += V P of unit u-1 and S of unit u+1 while the vector unit runs the softmax of unit u; the three have no
 // dependency on each other, so MFMA and VALU instructions alternate in one basic block (scheduling barriers and
 // value pins below hold the order).  Everything with control flow (raising the maximum, the first unit of a row, a
-// ragged key block, a key block whose V scale is far below the first one's) sits between the steps or in the
+// ragged key block, a key block whose V scale is far from the others') sits between the steps or in the
 // "careful" variant of a step.  In the middle of a list, where none of the special cases can occur (one bit per list
 // entry says so), iterations run in a form without guards.  What bounds the kernel: the issue of vector instructions beside
 // the MFMA, and on long bf16 launches the clock the chip grants (1.5 GHz).  Without the dot-product row sums (see lsum), at two
@@ -64,7 +64,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 // A lane raises the running maximum of its row when a weight of the current unit would exceed 2^kRaise times
 // the largest weight seen when the maximum was last set; fp16 holds 2^kRaise with room to spare (max 65504).
 constexpr float kRaise = 12.0f;
-// A key block whose V scale differs from that of the row's first block by more than 2^kTinyV either way, or is as far below
+// A key block whose V scale differs from the list's reference (its first scale) by more than 2^kTinyV either way, or is as far below
 // the largest one of the list so far, takes the careful step: its weights (or the factor that divides the scale out of the row
 // sums again) would leave the range of fp16, so its row sums are formed in fp32.
 constexpr float kTinyV = 8.0f;
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     int wbase = 0, d_j = 0;
     float d_lv = 0.f, d_cj = 0.f, lv_ref = 0.f;
     // One bit per window entry: set if its tile needs the guarded form of an iteration (past the end of the list,
-    // the ragged last block, a V scale far from the first tile's).
+    // the ragged last block, a V scale far from the others').
     unsigned long long d_bad = ~0ull, d_far = 0;         // (d_far: the last of these alone)
     float lv_top = -INFINITY;                            // largest V scale of the windows so far
     // k: number of leading valid entries of the list (a list taken from given labels may end in -1 entries)
@@ -453,7 +453,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     };
 
     // ---- pieces of a step.  Unit u of a wave is the 32-key half `half` of tile c: u = 2 c + half
-    // S^T of a unit: K rows 32 half .. 32 half + 31 of the tile in K slot c % 3
+    // S^T of a unit: K rows 32 half .. 32 half + 31 of the tile in a K slot
     // kbase / vbase: byte offset of a slot of the K ring / of the V^T ring (wave-uniform); the per-lane part koff / voff
     // is added once per slot, the half of the tile is an immediate offset of the read (K) or picks the register (V^T)
     auto k_frag_addr = [&](int kbase, int half, int s) {
@@ -761,7 +761,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
         else if (SL > 2 && c + 1 < k) wait_copies_and_barrier<T::VINS>();
         else wait_copies_and_barrier<0>();
         SLA_T(c, 1);
-        if (c + KAHEAD - wbase >= 64) load_window(wbase + 32);     // (never for lists of at most 64 blocks)
+        if (c + KAHEAD - wbase >= 64 && wbase + 64 < k) load_window(wbase + 32);     // (never for lists of at most 64 blocks)
         if (c + KAHEAD < k) request_K(c + KAHEAD, kreq);
         if (c + VAHEAD < k) request_V(c + VAHEAD, vreq);
         if (c + 1 == k) request_epilogue();
@@ -848,7 +848,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
 
     uint8_t *stA = lds + kHqOff, *stB = lds + kWtOff;
     const uint8_t *zrow = lds + T::ZOFF;
-    // ---- normalise the sparse output: the weights carried the V scale relative to the first tile's
+    // ---- normalise the sparse output: the weights carried the V scale relative to the list's reference
     const float inv_l = l_run > 0.f ? fast_exp2(lv_ref) / l_run : l_run;     // 0 for an empty list, NaN for a spoilt row
 #pragma unroll
     for (int e = 0; e < 2; ++e)

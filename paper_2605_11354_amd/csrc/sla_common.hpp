@@ -64,19 +64,12 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
     return __builtin_bit_cast(uint32_t, r);
 }
 
-__device__ __forceinline__ float bf16_round(float x) { return (float)(__bf16)x; }
-
 // exp2 on the hardware transcendental unit (v_exp_f32); exp2(-inf) = 0
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // value held by the lane 32 positions away (lanes l and l^32 exchange)
 __device__ __forceinline__ float xchg32(float v) { return __shfl_xor(v, 32, 64); }
 
-__device__ __forceinline__ float wave_max(float v)
-{
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
 // maximum over the wave, uniform (DPP row shifts, then the two row broadcasts; lane 63 ends with the result)
 template <int CTRL, int ROWS> __device__ __forceinline__ float dpp_max_step(float v)
 {
