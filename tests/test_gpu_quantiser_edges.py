@@ -1,6 +1,6 @@
 """The FP8 layer where the form of its two launches changes (rows that do not fill a group of 32, one and two passes over a
-row, half and whole groups per workgroup, the three token tiles, the fewest K steps), and the quantisers' division step on
-infinities and NaN, against the oracle or the stated formula (App. B.2: scale = max(amax, 1e-8) / 448, IEEE division,
+row, the last workgroup's half group, the three token tiles, the fewest K steps), and the quantisers' division step on
+infinities, NaN and very large operands, against the oracle or the stated formula (App. B.2: scale = max(amax, 1e-8) / 448, IEEE division,
 clamp, cast)."""
 import numpy as np
 import pytest
@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("N,d_in,d_out", [(1, 128, 8),                     # one row, one partial group of channels, two K steps
                                           (33, 1152, 72), (31, 2176, 264),  # slices held by fewer than four waves; two passes
-                                          (65, 2048, 136), (16000, 1152, 384),     # half groups / whole groups per workgroup, 8 slices a wave
+                                          (65, 2048, 136), (16000, 1152, 384),     # one row in the last group, whole groups; 8 slices a wave
                                           (4100, 256, 2048),               # 128-token tiles, four rows in the last one
                                           (8195, 128, 2056), (8200, 384, 2048)])   # 256-token tiles, two and six K steps
 def test_layer_at_the_edges_of_its_launches(oracle, N, d_in, d_out):
