@@ -296,7 +296,7 @@ def main() -> int:
         lflops = 2.0 * tokens * d_in * d_out
         out["fp8_linear"] = {"ms": round(lms, 5), "shape": [tokens, d_in, d_out], "bound": "mfma", "algorithmic_flops": lflops,
                              "achieved_TFLOPs": round(lflops / lms / 1e9, 1), "frac": round(lflops / lms / 1e9 / PEAK_TFLOPS["fp8"], 4),
-                             "note": "three launches: token quantiser, weight quantiser, E4M3 GEMM with the scales and bias in its epilogue"}
+                             "note": "two launches: the quantiser of tokens and weights, E4M3 GEMM with the scales and bias in its epilogue"}
         # the same layer with the attention's E4M3 block quantiser in the GEMM's epilogue, against layer + 3 quantiser calls
         if cfg.B == 1 or cfg.N % 256 == 0:                    # a token block may not straddle a GEMM tile
             c8 = [torch.empty((cfg.B, cfg.N, cfg.H, 64), dtype=torch.uint8, device="cuda") for _ in range(3)]

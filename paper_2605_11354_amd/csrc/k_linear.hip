@@ -118,12 +118,13 @@ __device__ unsigned long long sla_gemm_probe_times[16];
 // Workgroup tile 64 TB tokens x 128 channels, four waves as 2 x 2, wave tile 32 TB tokens x 64 channels = TB x 2 MFMA tiles.
 // The kernel forms D[o][i] (W as the A operand), so that four consecutive accumulator registers of a lane are four
 // consecutive channels of one token.  K steps of one slice, three stages in LDS, copies two to three steps ahead of the
-// products, one barrier per step (the schedule is written out at the loop).  TB = 4 holds 128 accumulators per wave and 75 KB of LDS: two workgroups share a CU, and the
-// start and the epilogue of one (which take as long as its products) run under the products of the other.  Measured on
-// 43968 x 1024 -> 3072: 143-150 us with the qkv epilogue (1.9 PFLOP/s), 165 us with bf16 output, against 292 and 190 us of
-// tiles of 256 x 256 at one workgroup per CU (sixteen fragment reads per thirty-two products, but a quarter of a tile's
-// life start and epilogue with nothing beside them, half of it with the quantiser, and 2064 tiles in nine rounds of 256).
-// What bounds it now: the matrix unit is busy 60 % of the cycles at a clock that falls to 1.2-1.5 GHz under this load.
+// products, one barrier per step (the schedule is written out at the loop).  TB = 4 holds 128 accumulators per wave and 75 KB
+// of LDS: two workgroups share a CU, and the start and the epilogue of one (which take as long as its products) run under the
+// products of the other.  Measured on 43968 x 1024 -> 3072: 143-150 us with the qkv epilogue (1.9 PFLOP/s), 165-170 us with bf16
+// output, against 292 and 190 us of tiles of 256 x 256 at one workgroup per CU (sixteen fragment reads per thirty-two products,
+// but a quarter of a tile's life start and epilogue with nothing beside them, half of it with the quantiser, and 2064 tiles in
+// nine rounds of 256).  What bounds it now: the clock, which falls to 1.2-1.5 GHz under this load; the matrix unit is busy 54 %
+// of the cycles (47 % with bf16 output), and a third of a tile's life is the quantiser's epilogue.
 //
 // QKV: the layer is the qkv projection in front of the attention (O = 3 H 64 output channels ordered [q|k|v][head][64])
 // and the epilogue, instead of storing y, quantises it per (head, token block) with the scaled E4M3 quantiser of
