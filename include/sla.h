@@ -91,6 +91,8 @@ sla_status_t sla_workspace_bytes(const sla_params_t *p, size_t *bytes);
  *   W_proj    in   bf16 [D_in, D_out] or [H, D_in, D_out] (right-multiplied, no bias)
  *   O         out  bf16 [B,H,N,D]
  *   labels    out  optional int8 [B,H,Nqb,Nkb]; NULL to skip
+ * A query row with NaN or +infinity among the logits of its critical blocks comes out NaN; it does not affect other rows
+ * beyond the block labels, which its block's mean decides.
  */
 sla_status_t sla_forward(const sla_params_t *p,
                          const void *Q, const void *K, const void *V,

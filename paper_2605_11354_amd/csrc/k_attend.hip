@@ -64,6 +64,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 // A lane raises the running maximum of its row when a weight of the current unit would exceed 2^kRaise times
 // the largest weight seen when the maximum was last set; fp16 holds 2^kRaise with room to spare (max 65504).
 constexpr float kRaise = 12.0f;
+constexpr float kTopW = 65504.0f;                      // largest fp16
 // A key block whose V scale differs from the list's reference (its first scale) by more than 2^kTinyV either way, or is as far below
 // the largest one of the list so far, takes the careful step: its weights (or the factor that divides the scale out of the row
 // sums again) would leave the range of fp16, so its row sums are formed in fp32.
@@ -529,9 +530,10 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     };
     // Careful form (first unit of a row, ragged or tiny-scale tiles): exact maximum of the unit, row sums in fp32
     // from weights that do not carry the V scale.
-    // A row with a NaN or +inf among its logits (infinities or NaN in its Q, or in K) comes out NaN, and must not touch the
-    // others: the row sums of the fast steps tell rows q and q + 16 apart by zeros in A, and 0 NaN = NaN.  So its weights are
-    // replaced by zeros, here and in front of a fast step (raise_reference), and its sum remembers.
+    // A row with a NaN or +inf among its logits (infinities or NaN in its Q, or in K), or with logits so large that the
+    // differences to their maximum round to more than a weight can hold (from 2^28 on), comes out NaN, and must not touch the
+    // others: the row sums of the fast steps tell rows q and q + 16 apart by zeros in A, and 0 NaN = 0 inf = NaN.  So its weights
+    // are replaced by zeros, here and in front of a fast step (raise_reference), and its sum remembers.
     auto softmax_careful = [&](f32x16 &s, const TileInfo &t, Weights &w) __attribute__((always_inline)) {
         const float top = pair_max_nan(max16_nan(s)) * t.cj + t.lsv;        // -inf if the lane's row sees no real key in this unit
         if (__ballot(top > m_run)) {
@@ -548,7 +550,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
             s[x] = pu * r;                                          // weight with it: what multiplies the scaled V^T
         }
         sum += xchg32(sum);
-        const bool spoilt = !(sum < INFINITY);
+        const bool spoilt = !(sum < INFINITY) || !(pair_max_nan(max16_nan(s)) <= kTopW);
         if (__ballot(spoilt)) {
 #pragma unroll
             for (int x = 0; x < 16; ++x) s[x] = spoilt ? 0.f : s[x];
@@ -724,14 +726,14 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_kernel(
     // the overflow checks could be left out, small weights lost bits, and every move of the window raised it again.  Keeping the
     // checks costs nothing: a layer of 16 heads x 43968 tokens 656 us with and 658 without them, 10992 tokens 98 and 99.)
     auto raise_reference = [&](const TileInfo &t) __attribute__((always_inline)) {
-        const float top = pair_max_nan(max16_nan(s_cur)) * t.cj + t.lsv;
-        const bool spoilt = !(top < INFINITY);
+        const float mx = pair_max_nan(max16_nan(s_cur)), top = mx * t.cj + t.lsv;
+        const float m_new = top < INFINITY ? fmaxf(m_run, top) : m_run;
+        const bool spoilt = !(fmaf(mx, t.cj, t.lsv - m_new) <= kRaise);             // (the step's own expression)
         if (__ballot(spoilt)) {
 #pragma unroll
             for (int x = 0; x < 16; ++x) s_cur[x] = spoilt ? -INFINITY : s_cur[x];
             l_full = spoilt ? __builtin_nanf("") : l_full;
         }
-        const float m_new = spoilt ? m_run : fmaxf(m_run, top);
         const float alpha = m_new == m_run ? 1.0f : fast_exp2(m_run - m_new);
         rescale(alpha);
         const _Float16 ah = (_Float16)alpha;

@@ -51,10 +51,15 @@ def test_query_rows_with_infinities_and_nan(oracle, bq, length, dtype):
             d["Q"][0, 0, r, r % 64] = bits
         else:
             d["Q"][0, 0, r, r % 64] = 0x7F                  # E4M3 has no infinities: NaN
+    huge = [300, 301, 450, 1000, 1001, 2222]                # and finite rows whose logits leave the resolution of fp32: anything, but alone
+    if dtype == "bf16":
+        for r, size in zip(huge, [1e30, -1e30, 3e38, -1e12, 3e9, 1e20]):
+            d["Q"][0, 0, r, :7 * (r % 2) + 1] = np.float32(size).view(np.uint32) >> 16
     _, sparse, whole = _run(cfg, d, lab, length)
     good = np.ones(cfg.N, bool)
     good[list(rows)] = False
     assert np.isnan(sparse[~good]).all() and np.isnan(whole[~good]).all()
+    good[huge] = dtype != "bf16"
     full = lambda part: part.reshape(-1, 64)[:cfg.N]
     for got, part in ((sparse, "O_sparse"), (whole, "O")):
         want = full(ref[part])
