@@ -14,7 +14,7 @@ LIB = os.path.join(HERE, "libsla.so")
 # the shader-clock and 100 MHz counters at the phase boundaries of its work; results are unchanged).  Only probe.py loads it.
 PROBE_LIB = os.path.join(HERE, "libsla_probe.so")
 PROBED = ["k_attend.hip", "k_linear.hip", "k_classify.hip"]
-SOURCES = ["sla_api.hip", "k_classify.hip", "k_states.hip", "k_aggregate.hip", "k_attend.hip", "k_backward.hip", "k_quant.hip", "k_linear.hip"]
+SOURCES = ["sla_api.hip", "k_classify.hip", "k_states.hip", "k_aggregate.hip", "k_attend.hip", "k_attend_short.hip", "k_backward.hip", "k_quant.hip", "k_linear.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-ffp-contract=off", "-Wall", "-Wextra",
          "-Wno-unused-parameter", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-mllvm", "-amdgpu-mfma-vgpr-form=1"]   # MFMA accumulators stay in VGPRs: no AGPR copy traffic
