@@ -105,7 +105,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
     constexpr int A = 0, B = 1;                         // the two groups
     constexpr uint32_t kNaN2 = 0x7E007E00u;             // two fp16 NaN
     __shared__ __attribute__((aligned(1024))) uint8_t lds[T::LDS];
-    // all kernel arguments in one batch of scalar loads (see attend_kernel)
+    // all kernel arguments in one batch of scalar loads (left to the compiler: a round trip in front of each first use)
     asm volatile("" ::"s"(Qp), "s"(Kp), "s"(Vp), "s"(lvs), "s"(sQ), "s"(sK), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(crit_idx),
                  "s"(k_c), "s"(Hq), "s"(WT), "s"(proj_per_head), "s"(phi), "s"(H), "s"(N), "s"(Nqb), "s"(Nkb), "s"(total), "s"(c_exp), "s"(O), "s"(O32));
     const long work = xcd_remap(blockIdx.x, total);
@@ -151,8 +151,8 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
 #pragma unroll
     for (int x = 0; x < 16; ++x) zero16[x] = 0.f;
     f32x16 oacc[2][2] = {{zero16, zero16}, {zero16, zero16}};
-    // Running state of the lane's two rows, as in attend_kernel: reference exponent, row sums of the fast steps (register 0;
-    // formed on the matrix unit from the fp16 weights with the masked ones as A operand) and of the careful ones.
+    // Running state of the lane's two rows: reference exponent, row sums of the steps (register 0; formed on the matrix unit
+    // from the fp16 weights with the masked ones as A operand) and of the units repair() made again.
     float m_run[2] = {-3.4028235e38f, -3.4028235e38f}, l_full[2] = {0.f, 0.f};
     f32x4 lsum[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
     float l_old[2] = {0.f, 0.f};                        // the row sum without the last unit
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
 
     // ragged block: only the last key block of the sequence can be short
     const int tail_rows = N & (kBK - 1), ragged_j = tail_rows ? Nkb - 1 : -1;
-    // the list: a window of 64 entries in lanes, as in attend_kernel
+    // the list: a window of 64 entries in lanes
     int wbase = 0, d_j = 0;
     // (log2 of its V scale, exp2 constant, what divides the V scale out of the row sums)
     float d_lv = 0.f, d_cj = 0.f, lv_ref = 0.f, lv_top = -INFINITY;
@@ -457,7 +457,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
     SLA_TP(62, 5);
 #define SLA_SB() __builtin_amdgcn_sched_barrier(0)
 #define SLA_PIN(...) asm volatile("" : __VA_ARGS__)
-    // Step of group X (see above) in issue order (see attend_kernel's fast_step: one MFMA, then a staggered share of the vector
+    // Step of group X (see above) in issue order (one MFMA, then a staggered share of the vector
     // work, held in place by data dependencies and scheduling barriers), X's unit being half `half` of tile t.  (jy, halfy, ty): the
     // other group's last unit.  kslot: K slot of the next slice, whose fragments step A reads and step B holds; vslot: V^T slot of X's unit,
     // whose fragments step A reads.
@@ -570,6 +570,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
             step(GA{}, P, t_cur, j_prv, kh, t_prv, k1, vslot, 0);
             requests(c, P);
             set_ones(t_cur.inv2);
+            SLA_T(c, 3);
             step(GB{}, P, t_cur, j_cur, kh, t_cur, k1, 0, 0);
         } else {
             constexpr int k1 = (2 * P + 1) * T::KSLICE, k2 = ((2 * P + 2) & 3) * T::KSLICE;
@@ -633,6 +634,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
 #pragma unroll
     for (int r = 0; r < GROUPS; ++r) {
         f32x16 lin[2] = {zero16, zero16};                  // the linear branch, projected
+        if (r == 0) SLA_TP(61, 1);
         if (Hq != nullptr) {
             bf16x8 hfr[4][2], wfr[4][2];                   // read in one go: their latency passes behind the arithmetic of phi(Q)
 #pragma unroll

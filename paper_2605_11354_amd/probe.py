@@ -74,7 +74,7 @@ def probe_attend(idx: int, per_tile: bool) -> None:
     pr, ep = t[62], t[61]
     print("prologue, cycles: start -> list length %d | -> copies requested %d | -> scales requested %d | -> all landed + barrier %d | "
           "-> first S %d | -> block 0 %d" % (pr[1] - pr[0], pr[2] - pr[1], pr[3] - pr[2], pr[4] - pr[3], pr[5] - pr[4], t[0, 0] - pr[5]))
-    print("epilogue, cycles: last block -> loop exit %d | last PV + 1/l %d | phi(Q) %d | linear-branch MFMAs %d | barrier %d | store %d"
+    print("epilogue, cycles: last block -> loop exit %d | last sums and PV %d | phi(Q) %d | linear branch, 1/l %d | first group's store %d | second group %d"
           % (ep[0] - t[nk - 1, 4] if nk == k_c else -1, ep[1] - ep[0], ep[2] - ep[1], ep[3] - ep[2], ep[4] - ep[3], ep[5] - ep[4]))
     probe_select_report(L, (cfg.N + cfg.bk - 1) // cfg.bk)
     nwg = min(32768, cfg.B * cfg.H * ((cfg.N + cfg.bq - 1) // cfg.bq))
