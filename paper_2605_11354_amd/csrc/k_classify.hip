@@ -437,10 +437,10 @@ struct MemberKeys {
 
 // Radix descent, eight bits at a time from the top, for up to two ranks at once (want[t] = rank t wanted) over the
 // keys of `keys`; while both ranks follow the same prefix one histogram serves both.  hist: two histograms of 256
-// counters and, from spare_at on, a spare word per lane, private to the wave.  Requires 1 <= k[t] <= number of keys.
+// counters and a spare word per lane, private to the wave.  Requires 1 <= k[t] <= number of keys.
 template <class Keys>
 __device__ __forceinline__ void radix_cuts(const Keys keys, const int (&k)[2], const bool (&want)[2],
-                                           uint32_t *hist, Cut (&cut)[2], bool probe = false, uint32_t spare_at = 512u)
+                                           uint32_t *hist, Cut (&cut)[2], bool probe = false)
 {
     const int lane = threadIdx.x & 63;
     int pass_ = 0;
@@ -448,7 +448,7 @@ __device__ __forceinline__ void radix_cuts(const Keys keys, const int (&k)[2], c
     uint32_t prefix[2] = {0u, 0u};
     int kk[2] = {k[0], k[1]};
     bool act[2] = {want[0], want[1]};
-    const uint32_t spare = spare_at + lane;           // (a caller that asks for one rank only needs one histogram: spare_at = 256)
+    const uint32_t spare = 512u + lane;
     for (int shift = 24; shift >= 0 && (act[0] || act[1]); shift -= 8) {
         const bool both = act[0] && act[1], two = both && prefix[0] != prefix[1];
         wave_lds_sync();
@@ -627,11 +627,9 @@ __device__ __forceinline__ void classify_row_wave(uint64_t (&key)[KPL], long row
 #pragma unroll
         for (int m = 0; m < KPL; ++m) w[m] = (m * 64 + lane < Nkb) ? (uint32_t)((s_max - key_to_logit(key[m])) * scale) : ~0u;
     }
-    // (one rank per descent: a single histogram, so that four workgroups of the fused kernel still fit a CU's LDS)
-    Cut cut[2] = {Cut{0u, 0, 0}, Cut{0u, 0, 0}}, c1[2];
-    const bool one[2] = {true, false};
-    if (want[0]) { const int k1[2] = {k_c, 0}; radix_cuts(RegKeys<KPL>{w}, k1, one, hist, c1, false, 256u); cut[0] = c1[0]; }
-    if (want[1]) { const int k1[2] = {k_keep, 0}; radix_cuts(RegKeys<KPL>{w}, k1, one, hist, c1, false, 256u); cut[1] = c1[0]; }
+    Cut cut[2] = {Cut{0u, 0, 0}, Cut{0u, 0, 0}};
+    const int k2[2] = {k_c, k_keep};
+    radix_cuts(RegKeys<KPL>{w}, k2, want, hist, cut);
     const bool whole = (!want[0] || cut[0].r == cut[0].n) && (!want[1] || cut[1].r == cut[1].n);
 
     uint64_t Tc = 0, Tn = 0;
@@ -690,7 +688,7 @@ __global__ __launch_bounds__(64) void select_kernel(const double *__restrict__ S
                                                     int8_t *__restrict__ lab_dense, int32_t *__restrict__ crit_idx,
                                                     float *__restrict__ Pc, double *__restrict__ S_dense, float sm_scale)
 {
-    __shared__ __align__(16) uint32_t hist[256 + 64];     // a histogram and a spare word per lane
+    __shared__ __align__(16) uint32_t hist[512 + 64];     // two histograms and a spare word per lane
     const long row = blockIdx.x;
     const int lane = threadIdx.x;
     const double *s = S + row * pitch;
@@ -711,24 +709,28 @@ __global__ __launch_bounds__(64) void select_kernel(const double *__restrict__ S
 // Fused classifier for rows of 65 to 256 key blocks (Nkb <= 64 KPL): block mean of Q, pooled logits and
 // classification in one launch.  A workgroup of four waves takes four consecutive query blocks of one
 // (b, h).  Lane d of wave w first forms channel d of the block mean of query block w (serial fp64 sum
-// over the tokens in ascending order, times 1/count).  Chunk of 64 key blocks by chunk, the K means are staged in LDS
-// (the next chunk already on its way in registers) and lane l of wave w runs the 64-step fma chain of
-// (query block w, key block l), reading its K mean and (a broadcast) the Q mean two channels per LDS access; the logits never
-// leave registers.  (The Q mean out of lane d by v_readlane: 128 scalar registers, most of them spilt between the chunks.)
-// 16 heads x 172 rows of 172 key blocks: 17.4 -> 15.2 us; all loads of a block in flight: 0.3-0.5 us of it.
+// over the tokens in ascending order, times 1/count).  Sixteen channels at a time, the K means of the whole head are staged
+// in LDS (the next sixteen already on their way in registers) and lane l of wave w advances the 64-step fma chains of
+// (query block w, key blocks l, 64 + l, ..) by them, reading K means and (a broadcast) the Q mean two channels per LDS access; the
+// logits never leave registers.  Bound: latency -- the whole launch is resident at once, and a third of a workgroup's time was
+// the LDS reads of the chains.  Staged by channels, a read of the Q mean serves all the lane's chains (KPL + 1 reads for KPL
+// chains where 64 key blocks at a time needed 2 KPL) and the chains run side by side; with both ranks of the
+// classification in one descent (classify_row_wave) 16 heads x 172 rows of 172 key blocks: 15.2 -> 13.5 us (0.3 of it the
+// descent).  Eight channels at a time: 14.9 (twice the barriers).  Q through LDS as whole rows, as for shorter rows:
+// 15.0 (its round trips are in series with the rest).
 template <int KPL, bool FP8>
-__global__ __launch_bounds__(256) void classify_fused_kernel(const void *__restrict__ Q, const float *__restrict__ sQ, RowMap rm,
+__global__ __launch_bounds__(256, KPL == 4 ? 3 : 4) void classify_fused_kernel(const void *__restrict__ Q, const float *__restrict__ sQ, RowMap rm,
                                                              const double *__restrict__ kbar, int N, int bq, int Nqb, int Nkb,
                                                              int k_c, int k_n, uint64_t *__restrict__ mbits, int lab_pitch,
                                                              int8_t *__restrict__ lab_dense, int32_t *__restrict__ crit_idx,
                                                              float *__restrict__ Pc, double *__restrict__ S_dense,
                                                              double *__restrict__ qbar_out, float sm_scale)
 {
-    constexpr int kPitch = 66;             // doubles per row of the K-mean buffer: 16-byte aligned rows, and the
-                                           // sixteen lanes of one 16-byte access pass cover all 64 banks once
-    __shared__ __align__(16) double ks[64 * kPitch];
+    constexpr int kCh = 16, kPitch = kCh + 2;   // channels of a piece; doubles per row of the K-mean buffer: 16-byte aligned rows, and
+                                           // the sixteen lanes of one 16-byte access pass cover all 64 banks once
+    __shared__ __align__(16) double ks[64 * KPL * kPitch];
     __shared__ __align__(16) double qm[4][kD];
-    __shared__ __align__(16) uint32_t hist[4][256 + 64];   // per wave: a histogram and a spare word per lane
+    __shared__ __align__(16) uint32_t hist[4][512 + 64];   // per wave: two histograms and a spare word per lane
     // every kernel argument is fetched here, in one batch of scalar loads (left to the compiler: a dozen round trips to the
     // scalar cache, each in front of the first use of an argument)
     asm volatile("" ::"s"(Q), "s"(sQ), "s"(rm.bs), "s"(rm.hs), "s"(rm.ts), "s"(rm.H), "s"(kbar), "s"(N), "s"(bq), "s"(Nqb), "s"(Nkb), "s"(k_c), "s"(k_n),
@@ -740,15 +742,15 @@ __global__ __launch_bounds__(256) void classify_fused_kernel(const void *__restr
     const long row = bh * Nqb + i;
     const double *kh = kbar + bh * (long)Nkb * kD;
 
-    double2 nx[8];                         // the chunk of K means on its way to LDS (two channels per lane and load)
-    auto load_chunk = [&](int m) {
+    double2 nx[2 * KPL];                   // the piece of K means on its way to LDS (two channels per lane and load)
+    auto load_piece = [&](int c) {
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const int idx = tid + 256 * r, j = m * 64 + (idx >> 5);
-            nx[r] = j < Nkb ? *(const double2 *)(kh + (long)j * kD + (idx & 31) * 2) : double2{0.0, 0.0};
+        for (int r = 0; r < 2 * KPL; ++r) {
+            const int idx = tid + 256 * r, j = idx >> 3;
+            nx[r] = j < Nkb ? *(const double2 *)(kh + (long)j * kD + c * kCh + (idx & 7) * 2) : double2{0.0, 0.0};
         }
     };
-    load_chunk(0);
+    load_piece(0);
 
     double mean = 0.0;
     if (rowok) {                           // 2-byte (1-byte) loads straight from global memory: LDS is the busy unit here
@@ -775,30 +777,38 @@ __global__ __launch_bounds__(256) void classify_fused_kernel(const void *__restr
     }
     qm[wave][lane] = mean;
 
+    double s[KPL];
+#pragma unroll
+    for (int m = 0; m < KPL; ++m) s[m] = 0.0;
+#pragma unroll 1
+    for (int c = 0; c < kD / kCh; ++c) {
+        __syncthreads();                   // previous piece consumed
+#pragma unroll
+        for (int r = 0; r < 2 * KPL; ++r) {
+            const int idx = tid + 256 * r;
+            *(double2 *)(ks + (idx >> 3) * kPitch + (idx & 7) * 2) = nx[r];
+        }
+        __syncthreads();
+        if (c + 1 < kD / kCh) load_piece(c + 1);
+#pragma unroll
+        for (int d = 0; d < kCh; d += 2) {
+            const double2 qv = *(const double2 *)(&qm[wave][c * kCh + d]);
+#pragma unroll
+            for (int m = 0; m < KPL; ++m) {
+                const double2 kv = *(const double2 *)(ks + (m * 64 + lane) * kPitch + d);
+                s[m] = fma(qv.x, kv.x, s[m]);
+                s[m] = fma(qv.y, kv.y, s[m]);
+            }
+        }
+    }
     uint64_t key[KPL];
 #pragma unroll
     for (int m = 0; m < KPL; ++m) {
-        __syncthreads();                   // previous chunk consumed
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const int idx = tid + 256 * r;
-            *(double2 *)(ks + (idx >> 5) * kPitch + (idx & 31) * 2) = nx[r];
-        }
-        __syncthreads();
-        if (m + 1 < KPL) load_chunk(m + 1);
-        double s = 0.0;
-#pragma unroll
-        for (int d = 0; d < kD; d += 2) {
-            const double2 kv = *(const double2 *)(ks + lane * kPitch + d);
-            const double2 qv = *(const double2 *)(&qm[wave][d]);
-            s = fma(qv.x, kv.x, s);
-            s = fma(qv.y, kv.y, s);
-        }
         const int j = m * 64 + lane;
         key[m] = ~0ull;
         if (rowok && j < Nkb) {
-            if (S_dense) S_dense[row * Nkb + j] = s;
-            key[m] = desc_key(s);
+            if (S_dense) S_dense[row * Nkb + j] = s[m];
+            key[m] = desc_key(s[m]);
         }
     }
     if (rowok)
