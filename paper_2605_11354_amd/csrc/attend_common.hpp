@@ -53,15 +53,27 @@ __device__ __forceinline__ float pair_max_nan(float v)
     return __builtin_elementwise_maximum(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// log2 of the V scale of a lane's list entry relative to the list's reference, which is that of the first entry that has one
-// (first: set it from this window).  A block of zeros (lv = -inf) fits any scale and takes the reference.
+// log2 of the V scale of a lane's list entry relative to the list's reference: the scale of the first entry that has one, or, if a finite
+// scale of this window lies more than 2^kFarV above that, the largest of them (first: set it from this window).  A block of zeros
+// (lv = -inf) fits any scale and takes the reference.  A block further than 2^kFarV below the reference counts as that far below:
+// its values vanish beside the reference's either way, and its weights, with the scale and without, keep within the range of fp32.
+constexpr float kFarV = 100.0f;
 __device__ __forceinline__ float relative_scale(float lv, bool in, bool first, float &lv_ref)
 {
     if (first) {
         const unsigned long long m = __ballot(in && lv != -INFINITY);
         lv_ref = m ? __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(lv), __builtin_ctzll(m))) : 0.f;
     }
-    return lv == -INFINITY ? 0.f : lv - lv_ref;
+    float d = lv == -INFINITY ? 0.f : lv - lv_ref;
+    if (__ballot(in && fabsf(d) > kFarV)) {
+        const bool above = first && in && lv < INFINITY && d > kFarV;
+        if (__ballot(above)) {
+            lv_ref = wave_max_dpp(above ? lv : -INFINITY);
+            d = lv == -INFINITY ? 0.f : lv - lv_ref;
+        }
+        d = d < -kFarV ? -kFarV : d;
+    }
+    return d;
 }
 
 // The lane index, computed here (two instructions) and not carried in a register from the top of the kernel

@@ -36,6 +36,10 @@ template <int N, bool FLIP> __device__ __forceinline__ void copy_nk_to_lds(const
     }
 }
 
+// The row sums are those of the weights with the V scale 2^lsv, divided by it, unless it is further than 2^kFarSum from the list's
+// reference: fp32 holds a scaled weight down to 2^-126 of the largest, one that counts in the sum (2^-30 of it) down to a scale of 2^-96.
+constexpr float kFarSum = 32.0f;
+
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 // largest of the 16 values a lane holds of one unit of S^T
 __device__ __forceinline__ float max16(const f32x16 &s)
@@ -285,7 +289,8 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
         const int valid = (int)j == ragged_j ? tail_rows : kBK;
         const float cj = FP8 ? __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(d_cj), c)) : c_exp;
         const float lsv = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(d_lv), c));
-        const float per_scale = fast_exp2(-lsv);
+        const bool far = !(fabsf(lsv) <= kFarSum);     // then the weights are summed without the V scale
+        const float per_scale = far ? 0.f : fast_exp2(-lsv);
         wait_copies_and_barrier<0>();                  // tile c has landed
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
@@ -314,22 +319,30 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
                     for (int x = 0; x < 16; ++x) oacc[e][x] *= alpha;
                 m_run = m_new;
             }
-            const float moff = lsv - (m_run == -INFINITY ? 0.f : m_run);
-            float sum = 0.f;                                           // of the weights with the V scale, which is divided out once
+            const float mfin = m_run == -INFINITY ? 0.f : m_run, moff = lsv - mfin;
+            auto real = [&](int x) { return 8 * (x >> 2) + (x & 3) < valid - 32 * half - 4 * g; };      // keys past the end get no weight
+            if (far) {
+                float plain = 0.f;
+#pragma unroll
+                for (int x = 0; x < 16; ++x) {
+                    const float e = fast_exp2(fmaf(sacc[x], cj, -mfin));
+                    plain += real(x) ? e : 0.f;
+                }
+                l_sum += plain;
+            }
+            float sum = 0.f;                                           // with the V scale, which is divided out once
 #pragma unroll
             for (int x = 0; x < 16; ++x) {
                 sacc[x] = fast_exp2(fmaf(sacc[x], cj, moff));
                 sum += sacc[x];
             }
             f16x8 p[2] = {pack8_f16(sacc, 0), pack8_f16(sacc, 8)};
-            if (valid != kBK) {                        // keys past the end get no weight
-                const int left = valid - 32 * half - 4 * g;
+            if (valid != kBK) {
                 sum = 0.f;
 #pragma unroll
                 for (int x = 0; x < 16; ++x) {
-                    const bool real = 8 * (x >> 2) + (x & 3) < left;
-                    sum += real ? sacc[x] : 0.f;
-                    p[x >> 3][x & 7] = real ? p[x >> 3][x & 7] : (_Float16)0.f;
+                    sum += real(x) ? sacc[x] : 0.f;
+                    p[x >> 3][x & 7] = real(x) ? p[x >> 3][x & 7] : (_Float16)0.f;
                 }
             }
             l_sum = fmaf(sum, per_scale, l_sum);
@@ -346,7 +359,7 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
 
     // ---- O = O_sparse / l + O_lin W
     const float l_run = l_sum + xchg32(l_sum);
-    const float inv_l = l_run > 0.f ? fast_exp2(lv_ref) / l_run : 0.f;
+    const float inv_l = l_run > 0.f ? fast_exp2(lv_ref) / l_run : l_run;     // 0 for an empty list, NaN for a spoilt row
 #pragma unroll
     for (int e = 0; e < 2; ++e)
 #pragma unroll

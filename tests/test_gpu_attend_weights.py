@@ -130,3 +130,26 @@ def test_values_of_far_apart_scales(oracle, bq, dtype, scales):
     err = max(_error(case, oracle, lab, [(0, 0)]), _error(case, oracle, lab, [(0, case.Nqb - 1)]))
     print(f"bq={bq} {dtype} {scales}: {err:.3e}")
     assert err <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("bq,dtype", [(64, "bf16"), (128, "bf16"), (64, "fp8"), (128, "fp8")])
+@pytest.mark.parametrize("scales", [(0, -120), (2, -126), (90, -40), (0, -60), (-120, 0), (-126, 2), (-40, 90), (2, -126, -126, 2, -60)])
+@pytest.mark.parametrize("tail", [64, 40])             # tokens of the last block
+def test_values_at_the_ends_of_the_range(oracle, bq, dtype, scales, tail):
+    """Values of 2^scales[j] in block j, up to the whole range of bf16 apart and in either order, two blocks (the short-list
+    kernel with 64-row query blocks) and five: a block whose values vanish beside another's still takes its share of the weight."""
+    rng = np.random.default_rng(len(scales) + tail)
+    N = 64 * len(scales) - 64 + tail
+    q, k, v = (rng.standard_normal((N, 64)) for _ in range(3))
+    v = v * np.float32(2.0) ** np.repeat(np.array(scales, np.float32), 64)[:N, None]
+    case = _case(q, k, v, bq, "bf16")
+    u = np.ascontiguousarray(v, dtype=np.float32).view(np.uint32)          # (values below 2^-20 stay)
+    d = dict(case.d, V=((u + 0x7FFF + ((u >> 16) & 1)) >> 16).astype(np.uint16)[None, None])
+    if dtype == "fp8":
+        for t, blk in (("Q", bq), ("K", 64), ("V", 64)):
+            d[t], d["s" + t] = synth.quantise_e4m3_blocks(d[t], blk)
+    case = G.Case(case.cfg.with_(dtype=dtype), {n: None if a is None else np.ascontiguousarray(a) for n, a in d.items()}, k_crit=len(scales), k_neg=0)
+    lab = np.full((1, 1, case.Nqb, case.Nkb), 2, np.int8)
+    err = _error(case, oracle, lab, [(0, i) for i in range(case.Nqb)])
+    print(f"bq={bq} {dtype} {scales} {tail}: {err:.3e}")
+    assert err <= 2.0 ** -8                                 # fp16 weights, 2^-11, on sums whose terms cancel to a few times that
