@@ -107,6 +107,28 @@ class Case:
                              d["sQ"], d["sK"], d["sV"], want_parts)
 
 
+def sparse_f32(case: Case, lab: np.ndarray, launch_blocks: int = 0) -> np.ndarray:
+    """The sparse branch's fp32 result [N,64] of a one-head case.  launch_blocks: the head is repeated until the launch has at
+    least so many query blocks; all its copies have to come out alike, bit for bit."""
+    heads = max(1, -(-launch_blocks // case.Nqb))
+    if heads > 1:
+        rep = lambda a: None if a is None else np.ascontiguousarray(np.repeat(a, heads, axis=1))
+        d = {n: rep(case.d[n]) for n in ("Q", "K", "V", "sQ", "sK", "sV")}
+        lab = rep(lab)
+        case = Case(case.cfg.with_(H=heads, proj_per_head=False), dict(d, W=case.d["W"][:1]), case.k_c, case.k_n, case.sm_scale)
+    O = torch.full((1, heads, case.cfg.N, 64), float("nan"), dtype=torch.float32, device="cuda")
+    B.sla_sparse_combine_f32(case.p, case.Q, case.K, case.V, None, torch.from_numpy(lab).cuda(), None, O, case.sQ, case.sK, case.sV, case.ws)
+    torch.cuda.synchronize()
+    bits = O.view(torch.int32)
+    assert bool((bits == bits[:, :1]).all()), "copies of one head differ"
+    return O[0, 0].cpu().numpy().astype(np.float64)
+
+
+# (query block, data type, query blocks of the launch) of attend_kernel's forms: 128-row blocks run on four waves in launches of
+# at most 768 blocks and on two waves in launches of 769 to 1024
+ATTEND_FORMS = [(64, "bf16", 0), (64, "fp8", 0), (128, "bf16", 0), (128, "fp8", 0), (128, "bf16", 769), (128, "fp8", 769)]
+
+
 def gather_blocks(O_full: np.ndarray, sel, bq: int, H: int) -> np.ndarray:
     """[B,H,N,64] -> [n_sel,bq,64] (rows past N zero) in the oracle's compact layout."""
     N = O_full.shape[2]

@@ -1,5 +1,5 @@
 """Infinities and NaN in Q or K stay in the rows whose softmax they reach: every other row of the attention kernel (Alg. 1
-steps 4-5) is that of the oracle, on lists that take the guarded and the guard-free iterations and more than one window, and
+steps 4-5) is that of the oracle, on lists of a few entries and of more than one window, in every form of the kernel, and
 on the short-list kernel."""
 import numpy as np
 import pytest
@@ -28,20 +28,20 @@ def _case(bq, dtype, nkb, length, seed):
     return cfg, d, lab
 
 
-def _run(cfg, d, lab, length):
+def _run(cfg, d, lab, length, launch=0):
     case = G.Case(cfg, d, k_crit=length, k_neg=0)
-    O = torch.full((1, 1, cfg.N, 64), 7.0, dtype=torch.float32, device="cuda")
+    sparse = G.sparse_f32(case, lab, launch)
     labd = torch.from_numpy(lab).cuda()
-    B.sla_sparse_combine_f32(case.p, case.Q, case.K, case.V, None, labd, None, O, case.sQ, case.sK, case.sV, case.ws)
     whole = torch.full((1, 1, cfg.N, 64), 7.0, dtype=torch.bfloat16, device="cuda")
     B.sla_forward_with_labels(case.p, case.Q, case.K, case.V, case.W, labd, whole, case.sQ, case.sK, case.sV, case.ws)
     torch.cuda.synchronize()
-    return case, O.cpu().numpy().astype(np.float64)[0, 0], G.bf16_tensor_to_f64(whole)[0, 0]
+    return case, sparse, G.bf16_tensor_to_f64(whole)[0, 0]
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
-@pytest.mark.parametrize("bq,length", [(64, 2), (64, 3), (64, 9), (64, 34), (64, 68), (128, 3), (128, 9), (128, 34), (128, 68)])
-def test_query_rows_with_infinities_and_nan(oracle, bq, length, dtype):
+@pytest.mark.parametrize("bq,length,launch", [(64, 2, 0), (64, 3, 0), (64, 9, 0), (64, 34, 0), (64, 68, 0), (128, 3, 0), (128, 9, 0), (128, 34, 0), (128, 68, 0),
+                                              (128, 3, 769), (128, 9, 769), (128, 68, 769)])
+def test_query_rows_with_infinities_and_nan(oracle, bq, length, launch, dtype):
     cfg, d, lab = _case(bq, dtype, 70, length, length)
     case, _, _ = _run(cfg, d, lab, length)
     ref = case.oracle_attend(oracle, lab, want_parts=True)
@@ -55,7 +55,7 @@ def test_query_rows_with_infinities_and_nan(oracle, bq, length, dtype):
     if dtype == "bf16":
         for r, size in zip(huge, [1e30, -1e30, 3e38, -1e12, 3e9, 1e20]):
             d["Q"][0, 0, r, :7 * (r % 2) + 1] = np.float32(size).view(np.uint32) >> 16
-    _, sparse, whole = _run(cfg, d, lab, length)
+    _, sparse, whole = _run(cfg, d, lab, length, launch)
     good = np.ones(cfg.N, bool)
     good[list(rows)] = False
     assert np.isnan(sparse[~good]).all() and np.isnan(whole[~good]).all()
@@ -68,9 +68,9 @@ def test_query_rows_with_infinities_and_nan(oracle, bq, length, dtype):
         assert (strict if part == "O_sparse" else err) <= G.TOL[dtype]
 
 
-@pytest.mark.parametrize("bq", [64, 128])
+@pytest.mark.parametrize("bq,launch", [(64, 0), (128, 0), (128, 769)])
 @pytest.mark.parametrize("length", [2, 9, 68])
-def test_keys_with_an_infinity(bq, length):
+def test_keys_with_an_infinity(bq, launch, length):
     """K[t][c] = +inf: rows with q[c] > 0 that attend to t see a logit of +inf (NaN out), rows with q[c] < 0 one of -inf (weight
     0), rows with q[c] = 0 NaN."""
     cfg, d, lab = _case(bq, "bf16", 70, length, 100 + length)
@@ -79,7 +79,7 @@ def test_keys_with_an_infinity(bq, length):
         d["K"][0, 0, t, c] = INF
         lab[0, 0, :, t // 64] = np.where(np.arange(lab.shape[2]) % 3 == 0, lab[0, 0, :, t // 64], 1)      # one row in three at most attends to it
     lab[0, 0, ::5, 0], lab[0, 0, ::5, 1:] = 2, np.where(np.cumsum(lab[0, 0, ::5, 1:] == 2, axis=1) < length, lab[0, 0, ::5, 1:], 1)
-    _, sparse, _ = _run(cfg, d, lab, length)
+    _, sparse, _ = _run(cfg, d, lab, length, launch)
     f = lambda b: (b.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
     q, k, v = f(d["Q"][0, 0]), f(d["K"][0, 0]), f(d["V"][0, 0])
     want = np.zeros((cfg.N, 64))

@@ -1,21 +1,19 @@
 """The attention kernel's units of 32 keys (Alg. 1 steps 4-5): lists of 0 to 6 blocks whose last block is ragged at either half
 of it, and query blocks that end in either half of their rows, with logits that pass the range of the fp16 weights in every unit
-(each is formed again with a raised reference), in some or in none, against the oracle on the fp32 result."""
+(each is formed again with a raised reference), in some or in none, in every form of the kernel, against the oracle on the fp32 result."""
 import numpy as np
 import pytest
-import torch
 
-from paper_2605_11354_amd import binding as B
 from paper_2605_11354_amd import synth
 from tests import gpu_util as G
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("bq,dtype", [(64, "bf16"), (128, "bf16"), (64, "fp8"), (128, "fp8")])
+@pytest.mark.parametrize("bq,dtype,launch", G.ATTEND_FORMS)
 @pytest.mark.parametrize("tail", [1, 31, 32, 33, 64])
 @pytest.mark.parametrize("binades", [0, 7, 20])        # by which a unit's exponents lie above those of the one before
-def test_ragged_units_and_raised_references(oracle, bq, dtype, tail, binades):
+def test_ragged_units_and_raised_references(oracle, bq, dtype, launch, tail, binades):
     rng = np.random.default_rng(100 * tail + binades)
     nkb = 13
     N = (nkb - 1) * 64 + tail
@@ -37,13 +35,11 @@ def test_ragged_units_and_raised_references(oracle, bq, dtype, tail, binades):
         if n and i % 2:
             js[-1] = nkb - 1                           # with the ragged block
         lab[0, 0, i, js] = 2
-    O = torch.full((1, 1, N, 64), float("nan"), dtype=torch.float32, device="cuda")
-    B.sla_sparse_combine_f32(case.p, case.Q, case.K, case.V, None, torch.from_numpy(lab).cuda(), None, O, case.sQ, case.sK, case.sV, case.ws)
-    torch.cuda.synchronize()
+    O = G.sparse_f32(case, lab, launch)
     ref = case.oracle_attend(oracle, lab, want_parts=True)
-    got = G.gather_blocks(O.cpu().numpy().astype(np.float64), ref["sel"], bq, 1)
+    got = G.gather_blocks(O[None, None], ref["sel"], bq, 1)
     err = np.abs(got - ref["O_sparse"]).max() / np.sqrt(np.mean(ref["O_sparse"] ** 2))
-    print(f"bq={bq} {dtype} tail={tail} binades={binades}: {err:.3e}")
+    print(f"bq={bq} {dtype} {launch} tail={tail} binades={binades}: {err:.3e}")
     # fp16 weights: 2^-11 each on sums that cancel to a few times that; logits of up to 520 binades: 520 x 2^-24 at each of a few
     # roundings, below 2^-12 of a weight
     assert err <= 2.0 ** -8

@@ -106,6 +106,30 @@ def test_forward_more_shapes(oracle, name, phi):
     assert torch.equal(tm(O).view(torch.int16), Ot.view(torch.int16))
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+def test_two_wave_form_with_the_linear_branch(oracle, dtype):
+    """100 heads x 8 query blocks of 128 rows, the last one ragged at a ragged key block: a launch of the two-wave form of the
+    attention kernel (more than 768 blocks), whole forward and given labels with lists of 0 to 5 blocks, a few heads against the oracle."""
+    cfg = (C4 if dtype == "fp8" else C0).with_(B=1, H=100, N=901, bq=128, proj_per_head=True)
+    case = G.Case(cfg, k_crit=5, k_neg=4)
+    rng = np.random.default_rng(9)
+    sel = [(h, i) for h in (0, 1, 57, 99) for i in range(case.Nqb)]
+    O, lab = case.forward()
+    refc = case.oracle_classify(oracle)
+    assert np.array_equal(lab.cpu().numpy(), refc["labels"])
+    ref = case.oracle_attend(oracle, refc["labels"], sel)
+    G.assert_output(G.gather_blocks(G.bf16_tensor_to_f64(O), ref["sel"], 128, 100), ref["O"], dtype, f"two waves, {dtype}")
+    given = rng.integers(0, 2, size=refc["labels"].shape).astype(np.int8)
+    for idx in np.ndindex(given.shape[:3]):
+        given[idx][rng.choice(case.Nkb, idx[2] % 6, replace=False)] = 2
+    O32, O16 = _f32_forward(case, given)
+    assert torch.equal(O32.to(torch.bfloat16).view(torch.int16), O16.view(torch.int16))
+    ref = case.oracle_attend(oracle, given, sel)
+    err = G.rel_err(G.gather_blocks(O32.cpu().numpy().astype(np.float64), ref["sel"], 128, 100), ref["O"])
+    print(f"[parity] two waves, given lists, {dtype}: {err:.3e}")
+    assert err <= G.TOL[dtype]
+
+
 def _requantise(cfg, d16):
     out = dict(d16)
     out["Q"], out["sQ"] = synth.quantise_e4m3_blocks(d16["Q"], cfg.bq)
@@ -192,7 +216,7 @@ def test_critical_lists_longer_than_a_window(oracle, bq, dtype):
 @pytest.mark.parametrize("bq", [64, 128])
 def test_v_blocks_of_very_different_magnitude(oracle, bq):
     """bf16 V whose key blocks differ by up to 2^32 in magnitude: the fp16 copy of V carries one power of two per
-    block and the weights its exponent; blocks far below / above the row's first block take the careful step."""
+    block and the weights its exponent; the row sums of blocks far below / above the row's first block are formed in fp32."""
     cfg = C0.with_(N=900, bq=bq, proj_per_head=True)
     d = dict(synth.make_inputs(cfg))
     f = lambda bits: (bits.astype(np.uint32) << 16).view(np.float32)
@@ -224,7 +248,7 @@ def test_running_maximum_raised_in_mid_list(oracle, bq, where):
     """Keys of one block scaled so that their logits tower over everything seen before: the attention kernel's
     running maximum, set by the first block, has to be raised when the list reaches that block (staircase: every
     block from the fourth to the twelfth towers over the one before, so the maximum is raised again and again in the
-    middle of the list, where the kernel runs its iterations without per-tile checks)."""
+    middle of the list)."""
     cfg = C0.with_(N=1100, bq=bq)
     d = dict(synth.make_inputs(cfg))
     f = lambda bits: (bits.astype(np.uint32) << 16).view(np.float32)
