@@ -36,6 +36,14 @@
 // other lanes before its exponentials.  Whether the reference has to be raised shows in the unit's row sums (formed on the matrix
 // unit from the fp16 weights), two instructions a unit; then the unit is repaired (see there).  A maximum over the exponents in front of
 // the exponentials, the form before, takes ten of the unit's 52 vector instructions, and vector issue is what bounds the loop.
+// A repair reads its keys again from global memory, some 4000 cycles with the wait of the other waves, so the tiles behind one are
+// prescanned (see there): where a logit has left the range another is likely to, and the maximum in front of them costs a tenth of that.
+// Tiles whose V scale is far from the list's are prescanned too, for their row sums.  Forward on given labels with 16 heads, against a repair
+// for every unit that passes 2^8 or is of such a tile: 43968 tokens, V of every second block 2^-10 of the others' 1270 -> 805 us; one
+// block in sixteen 752 -> 617; keys four times as long 674 -> 601, ten times 854 -> 676, growing along the sequence by twenty 1264 -> 720;
+// 60000 tokens in E4M3, the same five: 1622 -> 966, 968 -> 779, 830 -> 732, 1057 -> 800, 1587 -> 864; 10992 tokens in 64-row blocks 145 -> 108,
+// 112 -> 95, 113 -> 95, 134 -> 102, 140 -> 103.  (With a maximum in front of every unit instead, the form before: 43968 tokens 874, 661, 630,
+// 631, 684; E4M3 1226, 898, 771, 794, 878; 10992 tokens 112, 104, 89, 90, 93.)  Benign keys: 546 -> 549, 704 -> 699, 92 -> 90.
 //
 // Memory pipeline.  K and V^T tiles go from global memory straight into LDS (buffer loads, no staging registers).  K has four
 // slots of half a tile, V^T two of a tile: 33 KB, so that four workgroups fit a CU.  Iteration c (tile c) reads V^T tile c and, KS = 1,
@@ -67,15 +75,20 @@
 
 namespace sla {
 
-// A unit whose weights (V scale included) add up to more than this has the reference raised to its exact maximum.  fp16 would do
-// with anything below 2^16; the closer the largest weights are to the reference, the more often the largest one is 1 exactly, and the smaller the error
-// (2^16: 10 % more of it on peaked rows than 2^8, in the same time; 2^6: 2 % less, in 3 % more).
-constexpr float kRepair = 256.0f;
+// A unit whose weights (V scale included) add up to more than this has the reference raised to its exact maximum.  fp16 holds weights
+// below 2^16.  The closer the largest weights are to the reference, the more often the largest one is 1 exactly, and the smaller the error: with
+// 2^8 it is the same on the benchmark's keys, 14 % less on keys three times as long (1.03e-4 against 0.88e-4 of the result, 1.04e-4 with
+// an exact maximum wherever a weight passes 2^12), but such keys then repair often (43968 tokens, keys four times as long: 709 us against 601).
+constexpr float kRepair = 32768.0f;
+// A prescan raises the reference of rows with weights above 2^kAhead: 32 of those are within kRepair.
+constexpr float kAhead = 10.0f;
+// Tiles that are prescanned behind a repair, or a prescan that raised.  (Four: 627 us instead of 601 on the keys above, no difference on others.)
+constexpr int kHot = 2;
 // A row is spoilt (see repair) if its largest exponent lies this far above its own maximum.
 constexpr float kSpoilt = 12.0f;
-// A key block whose V scale differs from the list's reference (its first scale) by more than 2^kTinyV either way, or is as far below
-// the largest one of the list so far, is special: the factor that divides the scale out of the row sums again would leave the range of
-// fp16, so its row sums are formed in fp32.
+// A key block whose V scale differs from the list's reference by more than 2^kTinyV either way, or is as far below the largest one
+// of the list so far: the factor that divides the scale out of the row sums again would leave the range of fp16, so they are formed
+// in fp32 (prescan).
 constexpr float kTinyV = 8.0f;
 
 // RH row halves of 64 rows times KS parts of the keys: one wave each
@@ -166,6 +179,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
     // (log2 of its V scale, exp2 constant, what divides the V scale out of the row sums)
     float d_lv = 0.f, d_cj = 0.f, lv_ref = 0.f, lv_top = -INFINITY;
     uint32_t d_inv2 = 0u;
+    unsigned long long d_far = 0;                       // entries whose V scale is far from the reference
     float d_lim = 0.f;                                  // kRepair in units of the row sums
     int k = 0;                                          // leading valid entries
     {
@@ -193,9 +207,10 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
         lv_top = fmaxf(lv_top, wave_max_dpp(wbase + lane < k ? d_lv : -INFINITY));
         const bool far = !(fabsf(d_lv) <= kTinyV) || d_lv < lv_top - kTinyV;
         const float r = fast_exp2(-d_lv);
-        // as two fp16; NaN for a special tile (ragged, or a V scale far from the others'), which makes the row sums of its units NaN
-        // and sends them to repair
-        d_inv2 = far || d_j == ragged_j ? kNaN2 : pack_f16(r, r);
+        // as two fp16; NaN for a ragged tile, which makes the row sums of its units NaN and sends them to repair; 0 for a V scale far from
+        // the others': prescan forms the row sums
+        d_inv2 = d_j == ragged_j ? kNaN2 : far ? 0u : pack_f16(r, r);
+        d_far = __ballot(d_inv2 == 0u);
         d_lim = kRepair * r;
     };
     // softmax scale * log2(e) (* Q and K block scales for e4m3)
@@ -300,6 +315,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
     VFrag vf[2];                                        // by half of the tile
     f16x8 w[2][2];                                      // fp16 weights of a group's last unit [group][16-key step]
     f32x16 sacc[2];
+    int hot = 0, plain = 0;                             // tiles to prescan after a repair; those in front of `plain` need none
     auto load_kfrag = [&](int slot) __attribute__((always_inline)) {
 #pragma unroll
         for (int s = 0; s < (FP8 ? 2 : 4); ++s) kf.w[s] = *(const i32x4 *)(lds + (slot + koff[s]));
@@ -310,7 +326,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
 #pragma unroll
             for (int e = 0; e < 2; ++e) vf[b].f[ss][e] = *(const f16x8 *)(lds + e * 32 * 128 + (vbase + (voff[ss] ^ (half << 6))));
     };
-    auto s_product = [&](int r, int st, const f32x16 &acc) __attribute__((always_inline)) {
+    auto s_product = [&](int r, int st, const f32x16 &acc, const KFrag &kf) __attribute__((always_inline)) {
         if constexpr (FP8) {
             i32x8 k8;
             k8[0] = kf.w[0][0]; k8[1] = kf.w[0][1]; k8[2] = kf.w[0][2]; k8[3] = kf.w[0][3];
@@ -318,12 +334,13 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
             return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(k8, q8[r], acc, 0, 0, 0, 0, 0, 0);
         } else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf.w[st]), qf[r][st], acc, 0, 0, 0);
     };
-    auto compute_S = [&](int r) __attribute__((always_inline)) {
+    auto products = [&](int r, const KFrag &k) __attribute__((always_inline)) {
         f32x16 s = zero16;
 #pragma unroll
-        for (int st = 0; st < (FP8 ? 1 : 4); ++st) s = s_product(r, st, s);
+        for (int st = 0; st < (FP8 ? 1 : 4); ++st) s = s_product(r, st, s, k);
         return s;
     };
+    auto compute_S = [&](int r) __attribute__((always_inline)) { return products(r, kf); };
     // row sums of the unit whose weights are in w[r]
     auto add_rows = [&](int r, int ss) __attribute__((always_inline)) { lsum[r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, w[r][ss], lsum[r], 0, 0, 0); };
     // O^T += V^T P^T of a unit
@@ -334,14 +351,38 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
             for (int e = 0; e < 2; ++e) oacc[r][e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[half].f[ss][e], w[r][ss], oacc[r][e], 0, 0, 0);
     };
     // After the step of a unit of group r (half `half` of tile t in key block j), in front of the products that consume its weights:
-    // weights far above the reference, beyond the range of fp16 even, or NaN, show in the unit's row sums, and so does a special tile.  That
+    // weights far above the reference, beyond the range of fp16 even, or NaN, show in the unit's row sums, and so does a ragged tile.  That
     // is the overflow check (a subtraction and a comparison a unit, where a maximum over the exponents takes ten instructions); when
-    // it fires -- a few times per list, as larger logits turn up -- S^T is formed once more from the keys in global memory, the running maximum raised
-    // to the exact maximum over the unit (accumulators and row sums are rescaled), and the weights and their sums are formed again:
-    // keys past the end of a ragged block get no weight, the row sums of a special tile are formed in fp32 from weights without the
-    // V scale.  A row with a NaN or +inf among its logits, or with logits so large that the differences to their maximum round to
-    // more than a weight can hold, comes out NaN and must not touch the others (0 NaN = NaN in the row sums on the matrix unit):
-    // its weights become zeros and its sum remembers.
+    // it fires S^T is formed once more from the keys in global memory, the running maximum raised to the exact maximum over the unit
+    // (accumulators and row sums are rescaled), and the weights and their sums are formed again: keys past the end of a ragged block get
+    // no weight, its row sums are formed in fp32 from weights without the V scale.  A row with a NaN or +inf among its logits, or with
+    // logits so large that the differences to their maximum round to more than a weight can hold, comes out NaN and must not touch
+    // the others (0 NaN = NaN in the row sums on the matrix unit): its weights become zeros and its sum remembers.
+    // The reference of group r raised to `top` where that is finite and above it; what the accumulators were multiplied by
+    auto raise = [&](int r, float top) __attribute__((always_inline)) {
+        const float m_new = top < INFINITY ? fmaxf(m_run[r], top) : m_run[r];
+        const float lower = fast_exp2(m_run[r] - m_new), alpha = m_new == m_run[r] ? 1.0f : lower;
+        m_run[r] = m_new;
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int x = 0; x < 16; ++x) oacc[r][e][x] *= alpha;
+        return alpha;
+    };
+    // A spoilt row stays NaN whatever follows: without its Q it raises no more alarms
+    auto forget = [&](int r, bool spoilt) __attribute__((always_inline)) {
+        if constexpr (FP8) {
+#pragma unroll
+            for (int v = 0; v < 8; ++v) q8[r][v] = spoilt ? 0 : q8[r][v];
+        } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                uint4 q = __builtin_bit_cast(uint4, qf[r][v]);
+                q.x = spoilt ? 0u : q.x; q.y = spoilt ? 0u : q.y; q.z = spoilt ? 0u : q.z; q.w = spoilt ? 0u : q.w;
+                qf[r][v] = __builtin_bit_cast(bf16x8, q);
+            }
+        }
+    };
     // (kf is lost.)
     auto repair = [&](int r, uint32_t j, int half, const TileInfo &t) __attribute__((always_inline)) {
         const int ln = lane_now(), rows = (int)j == ragged_j ? tail_rows : kBK;
@@ -353,19 +394,14 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
 #pragma unroll
         for (int x = 0; x < 16; ++x) s[x] = 8 * (x >> 2) + (x & 3) < left ? s[x] : -INFINITY;
         const float mx = pair_max_nan(max16_nan(s)), top = mx * t.cj + t.lsv;      // -inf if the lane's row sees no real key in this unit
-        const float m_new = top < INFINITY ? fmaxf(m_run[r], top) : m_run[r];
-        const float lower = fast_exp2(m_run[r] - m_new), alpha = m_new == m_run[r] ? 1.0f : lower;
-        m_run[r] = m_new;
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
-#pragma unroll
-            for (int x = 0; x < 16; ++x) oacc[r][e][x] *= alpha;
+        const float alpha = raise(r, top), m_new = m_run[r];
         const bool special = t.inv2 == kNaN2;
         float sum = 0.f;                                    // weights without the V scale
+        if (special) {
 #pragma unroll
-        for (int x = 0; x < 16; ++x) sum += fast_exp2(fmaf(s[x], t.cj, -m_new));
-        sum += xchg32(sum);
-        sum = special ? sum : 0.f;
+            for (int x = 0; x < 16; ++x) sum += fast_exp2(fmaf(s[x], t.cj, -m_new));
+            sum = pair_sum(sum);
+        }
         const bool spoilt = !(fmaf(mx, t.cj, t.lsv - m_new) <= kSpoilt) || !(sum < INFINITY);
 #pragma unroll
         for (int x = 0; x < 16; ++x) {
@@ -376,10 +412,53 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
         w[r][1] = pack8_f16(s, 8);
         l_full[r] = spoilt ? __builtin_nanf("") : fmaf(l_full[r], alpha, sum);
         lsum[r] = f32x4{l_old[r] * alpha, 0.f, 0.f, 0.f};
+        forget(r, spoilt);
+        if (!special) { hot = kHot; plain = 0; }
         const uint32_t o = special ? 0u : ones_mask & t.inv2;
         const f16x8 own = __builtin_bit_cast(f16x8, make_uint4(o, o, o, o));
 #pragma unroll
         for (int ss = 0; ss < 2; ++ss) lsum[r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(own, w[r][ss], lsum[r], 0, 0, 0);
+    };
+    // In front of the units of a tile that is not ragged: the exact maximum over all of it, and the reference raised to that where weights
+    // would pass 2^kAhead.  Of a tile whose V scale is far from the list's (inv2 = 0) also the row sums, in fp32 from weights without the
+    // scale.  kslot: K slot of the tile's second half (KS = 1; the first is in kf).
+    auto prescan = [&](const TileInfo &t, int kslot) __attribute__((always_inline)) {
+        KFrag k2;
+        if constexpr (KS == 1) {
+#pragma unroll
+            for (int s = 0; s < (FP8 ? 2 : 4); ++s) k2.w[s] = *(const i32x4 *)(lds + (kslot + koff[s]));
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            float mx = max16_nan(r == A ? sacc[A] : compute_S(B));
+            if (KS == 1) mx = __builtin_elementwise_maximum(mx, max16_nan(products(r, k2)));
+            mx = pair_max_nan(mx);
+            const float top = mx * t.cj + t.lsv;
+            if (__ballot(!(top <= m_run[r] + kAhead))) {
+                const float alpha = raise(r, top);
+                const bool spoilt = !(fmaf(mx, t.cj, t.lsv - m_run[r]) <= kSpoilt);
+#pragma unroll                                              // (B's last unit is still to be added)
+                for (int x = 0; x < 16; ++x) w[r][x >> 3][x & 7] = (_Float16)((float)w[r][x >> 3][x & 7] * alpha);
+                l_full[r] = spoilt ? __builtin_nanf("") : l_full[r] * alpha;
+                lsum[r][0] *= alpha;
+                if (r == A) {
+#pragma unroll
+                    for (int x = 0; x < 16; ++x) sacc[A][x] = spoilt ? -INFINITY : sacc[A][x];
+                }
+                forget(r, spoilt);
+                hot = kHot;
+            }
+            if (t.inv2 == 0u) {                             // the sums without the V scale
+                float sum = 0.f;
+#pragma unroll
+                for (int h = 0; h < (KS == 1 ? 2 : 1); ++h) {
+                    const f32x16 s = h ? products(r, k2) : r == A ? sacc[A] : compute_S(B);
+#pragma unroll
+                    for (int x = 0; x < 16; ++x) sum += fast_exp2(fmaf(s[x], t.cj, -m_run[r]));
+                }
+                l_full[r] += pair_sum(sum);
+            }
+        }
     };
     auto needs_repair = [&](int r, const TileInfo &t) __attribute__((always_inline)) { return __ballot(!(lsum[r][0] - l_old[r] <= t.lim)) != 0; };
 
@@ -433,7 +512,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
     if (KS == 2) vf[0] = vf[1];
     TileInfo t_cur = tile_info(0), t_prv = t_cur, t_nxt;
     uint32_t j_prv = 0;
-    // S^T of A's first unit.  The reference of both groups starts as the exact maximum over their first unit (a special tile sets it in
+    // S^T of A's first unit.  The reference of both groups starts as the exact maximum over their first unit (a ragged tile sets it in
     // repair), KS = 1: over their first two: with one the error against 64 bits was 1 to 3 % larger, as the largest weight of a row is then
     // less often the reference itself, a weight of exactly 1.  (KS = 2: two waves have a first unit each.)
     f32x16 second[2] = {zero16, zero16};
@@ -468,7 +547,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
         uint32_t pw[8];
         float moff = t.lsv - m_run[X];
         auto pv = [&](int ss, int e) { oacc[Y][e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[X == A ? b ^ 1 : b].f[ss][e], w[Y][ss], oacc[Y][e], 0, 0, 0); };
-        auto sm = [&](int st) { sn = s_product(Y, st, sn); };
+        auto sm = [&](int st) { sn = s_product(Y, st, sn, kf); };
         auto fm = [&](int x0, int x1) {
 #pragma unroll
             for (int x = x0; x <= x1; ++x) s[x] = fmaf(s[x], t.cj, moff);
@@ -556,6 +635,11 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
             request_K(k_descriptor(j_nxt, 0), 2 * P * T::KSLICE);
         } else request_epilogue(P);
     };
+    // c: the next tile
+    auto set_plain = [&](int c) __attribute__((always_inline)) {
+        const unsigned long long far = d_far >> ((c - wbase) & 63);
+        plain = hot > 0 ? 0 : far ? c + __builtin_ctzll(far) : k;
+    };
     auto iteration = [&](int c, auto phase) __attribute__((always_inline)) {
         constexpr int P = decltype(phase)::value;
         constexpr int vslot = T::VRING + P * T::VBYTES;
@@ -565,6 +649,11 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
         const uint32_t j_cur = entry_j(c);
         t_nxt = tile_info(min(c + 1, k - 1));
         SLA_T(c, 2);
+        if (__builtin_expect(c >= plain, 0)) {
+            hot -= hot > 0;
+            if (t_cur.inv2 != kNaN2) prescan(t_cur, (2 * P + 1) * T::KSLICE);
+            set_plain(c + 1);
+        }
         if constexpr (KS == 2) {
             constexpr int k1 = 2 * (P ^ 1) * T::KSLICE;
             step(GA{}, P, t_cur, j_prv, kh, t_prv, k1, vslot, 0);
@@ -590,6 +679,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
         // the window: an iteration's requests reach two tiles ahead (never moves for lists of at most 64 blocks)
         if (c + 2 - wbase >= 64 && wbase + 64 < k) load_window(wbase + 32);
         const int end = k - wbase > 64 ? wbase + 62 : k;
+        set_plain(c);
         do {                                               // two iterations, so that slots are constants
             iteration(c, std::integral_constant<int, 0>{});
             if (++c == end) break;

@@ -1,7 +1,7 @@
 """The attention kernel's lists (Alg. 1 steps 4-5): lengths around the points where the window of 64 entries moves (an iteration
-reads two entries ahead of its own, the window moves by 32), odd and even (iterations run in pairs), with logits that hardly ever, now
-and then and often add up to more than the 2^8 per unit above which the reference is raised, in every form of the kernel, against the
-oracle on the fp32 result."""
+reads two entries ahead of its own, the window moves by 32), odd and even (iterations run in pairs), with logits whose weights never (gains
+1 and 1.3), now and then and often add up to more than the 2^15 per unit above which the reference is raised, in every form of the
+kernel, against the oracle on the fp32 result."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("bq,dtype,launch", G.ATTEND_FORMS)
-@pytest.mark.parametrize("gain", [1.0, 1.3, 5.0])      # of K: the reference is hardly ever, sometimes, often raised
+@pytest.mark.parametrize("gain", [1.0, 1.3, 5.0, 15.0])      # of K
 def test_list_lengths_and_raised_references(oracle, bq, dtype, launch, gain):
     cfg = synth.CONFIGS[1].with_(H=1, N=75 * 64 - 9, bq=bq)
     d = dict(synth.make_inputs(cfg))

@@ -68,6 +68,21 @@ def test_query_rows_with_infinities_and_nan(oracle, bq, length, launch, dtype):
         assert (strict if part == "O_sparse" else err) <= G.TOL[dtype]
 
 
+@pytest.mark.parametrize("bq,dtype,launch", G.ATTEND_FORMS)
+def test_a_nan_row_in_every_group_of_rows(oracle, bq, dtype, launch):
+    """One query in sixteen is NaN, so that no wave has a group of rows without one."""
+    cfg, d, lab = _case(bq, dtype, 20, 9, 5)
+    case, _, _ = _run(cfg, d, lab, 9)
+    want = case.oracle_attend(oracle, lab, want_parts=True)["O_sparse"].reshape(-1, 64)[:cfg.N]
+    d["Q"][0, 0, 3::16, 7] = NAN if dtype == "bf16" else 0x7F
+    _, sparse, _ = _run(cfg, d, lab, 9, launch)
+    bad = np.arange(cfg.N) % 16 == 3
+    assert np.isnan(sparse[bad]).all()
+    err, _ = G.output_error(sparse[~bad], want[~bad])
+    print(f"bq={bq} {dtype} {launch}: {err:.3e}")
+    assert err <= G.TOL[dtype]
+
+
 @pytest.mark.parametrize("bq,launch", [(64, 0), (128, 0), (128, 769)])
 @pytest.mark.parametrize("length", [2, 9, 68])
 def test_keys_with_an_infinity(bq, launch, length):
