@@ -164,12 +164,15 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
 #pragma unroll
     for (int x = 0; x < 16; ++x) zero16[x] = 0.f;
     f32x16 oacc[2][2] = {{zero16, zero16}, {zero16, zero16}};
-    // Running state of the lane's two rows: reference exponent, row sums of the steps (register 0; formed on the matrix unit
-    // from the fp16 weights with the masked ones as A operand) and of the units repair() made again.
+    // Running state of the lane's two rows: reference exponent, row sums of the steps (formed on the matrix unit from the fp16 weights,
+    // with 2^-scale as A operand where a row and a chunk of K belong together) and of the units repair() made again or prescan() summed.
+    // For bf16 V that factor is a power of two; an E4M3 block's is not, and its rounding to fp16 would be an error of up to 2^-12 on all the
+    // block's weights in the row sum.  So what fp16 leaves of it is the operand of a second row: register 0 has the sum, 1 the correction.
     float m_run[2] = {-3.4028235e38f, -3.4028235e38f}, l_full[2] = {0.f, 0.f};
     f32x4 lsum[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-    float l_old[2] = {0.f, 0.f};                        // the row sum without the last unit
-    const uint32_t ones_mask = ((lane & 3) == 0 && (((lane >> 2) ^ (lane >> 4)) & 1) == 0) ? ~0u : 0u;
+    float l_old[2][2] = {{0.f, 0.f}, {0.f, 0.f}};       // the two without the last unit
+    // which half of TileInfo::inv2 this lane's operand repeats (a v_perm selector; 12: a zero byte)
+    const uint32_t ones_sel = (((lane >> 2) ^ (lane >> 4)) & 1) || (lane & 2) ? 0x0c0c0c0cu : (lane & 1) ? 0x03020302u : 0x01000100u;
     f16x8 ones;
 
     // ragged block: only the last key block of the sequence can be short
@@ -207,9 +210,9 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
         lv_top = fmaxf(lv_top, wave_max_dpp(wbase + lane < k ? d_lv : -INFINITY));
         const bool far = !(fabsf(d_lv) <= kTinyV) || d_lv < lv_top - kTinyV;
         const float r = fast_exp2(-d_lv);
-        // as two fp16; NaN for a ragged tile, which makes the row sums of its units NaN and sends them to repair; 0 for a V scale far from
-        // the others': prescan forms the row sums
-        d_inv2 = d_j == ragged_j ? kNaN2 : far ? 0u : pack_f16(r, r);
+        // in fp16 and what that leaves; NaN for a ragged tile, which makes the row sums of its units NaN and sends them to repair; 0 for a V
+        // scale far from the others': prescan forms the row sums
+        d_inv2 = d_j == ragged_j ? kNaN2 : far ? 0u : pack_f16(r, FP8 ? r - (float)(_Float16)r : 0.f);
         d_far = __ballot(d_inv2 == 0u);
         d_lim = kRepair * r;
     };
@@ -299,7 +302,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
     // ---- per-tile constants (wave-uniform)
     struct TileInfo { float cj, lsv, lim; uint32_t inv2; };
     auto set_ones = [&](uint32_t inv2) __attribute__((always_inline)) {
-        uint32_t w = ones_mask & inv2;
+        const uint32_t w = __builtin_amdgcn_perm(inv2, inv2, ones_sel);
         ones = __builtin_bit_cast(f16x8, make_uint4(w, w, w, w));
         asm volatile("" : "+v"(ones));                      // (four registers, and not copies in front of every use)
     };
@@ -411,10 +414,10 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
         w[r][0] = pack8_f16(s, 0);
         w[r][1] = pack8_f16(s, 8);
         l_full[r] = spoilt ? __builtin_nanf("") : fmaf(l_full[r], alpha, sum);
-        lsum[r] = f32x4{l_old[r] * alpha, 0.f, 0.f, 0.f};
+        lsum[r] = f32x4{l_old[r][0] * alpha, FP8 ? l_old[r][1] * alpha : 0.f, 0.f, 0.f};
         forget(r, spoilt);
         if (!special) { hot = kHot; plain = 0; }
-        const uint32_t o = special ? 0u : ones_mask & t.inv2;
+        const uint32_t o = special ? 0u : __builtin_amdgcn_perm(t.inv2, t.inv2, ones_sel);
         const f16x8 own = __builtin_bit_cast(f16x8, make_uint4(o, o, o, o));
 #pragma unroll
         for (int ss = 0; ss < 2; ++ss) lsum[r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(own, w[r][ss], lsum[r], 0, 0, 0);
@@ -441,6 +444,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
                 for (int x = 0; x < 16; ++x) w[r][x >> 3][x & 7] = (_Float16)((float)w[r][x >> 3][x & 7] * alpha);
                 l_full[r] = spoilt ? __builtin_nanf("") : l_full[r] * alpha;
                 lsum[r][0] *= alpha;
+                if (FP8) lsum[r][1] *= alpha;
                 if (r == A) {
 #pragma unroll
                     for (int x = 0; x < 16; ++x) sacc[A][x] = spoilt ? -INFINITY : sacc[A][x];
@@ -460,7 +464,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
             }
         }
     };
-    auto needs_repair = [&](int r, const TileInfo &t) __attribute__((always_inline)) { return __ballot(!(lsum[r][0] - l_old[r] <= t.lim)) != 0; };
+    auto needs_repair = [&](int r, const TileInfo &t) __attribute__((always_inline)) { return __ballot(!(lsum[r][0] - l_old[r][0] <= t.lim)) != 0; };
 
     // ---- prologue: the first copies, the scales, Q
     if (k == 0) request_epilogue(0);
@@ -566,7 +570,8 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
         };
         SLA_SB();
         if constexpr (X == A) load_vfrag(b, vslot, half);
-        l_old[Y] = lsum[Y][0];
+        l_old[Y][0] = lsum[Y][0];
+        if (FP8) l_old[Y][1] = lsum[Y][1];
         if (!FP8) {
             sm(0);          fm(0, 2);   ex(0, 0);
             SLA_PIN("+v"(sn), "+v"(moff)); SLA_SB();
@@ -692,7 +697,8 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
     wait_copies_and_barrier<0>();                          // epilogue operands landed; every wave is past its last tile
     const int elane = lane_now(), e32 = elane & 31, eg = elane >> 5;         // (the loop carries no lane index)
     SLA_TP(61, 0);
-    l_old[B] = lsum[B][0];
+    l_old[B][0] = lsum[B][0];
+    l_old[B][1] = lsum[B][1];
     add_rows(B, 0);
     add_rows(B, 1);
     if (__builtin_expect(needs_repair(B, t_prv), 0)) repair(B, j_prv, KS == 2 ? kh : 1, t_prv);
@@ -702,7 +708,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
     uint8_t *ot = lds + T::VRING + PL * T::VBYTES + wave_u * 4096;           // the last V^T tile's slot: nobody reads it any more
     float l_run[2];
 #pragma unroll
-    for (int r = 0; r < 2; ++r) l_run[r] = lsum[r][0] + l_full[r];
+    for (int r = 0; r < 2; ++r) l_run[r] = lsum[r][0] + (FP8 ? lsum[r][1] : 0.f) + l_full[r];
     // KS = 2: the two waves that share rows exchange a group each (accumulators, reference exponent and row sums): what a wave has of its
     // group B is the other one's A.  It is left in LDS here and taken behind the linear branch, whose arithmetic hides the way.
     // Two waves: wave 0 leaves its 8 KB in the last V^T tile's slot, wave 1 in the free part of the K ring.

@@ -3,6 +3,7 @@ fp32 result, in every form of the kernel: rows with one dominant key of no value
 64 entries to the next in directions the queries do not see, and blocks of values of very different size."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2605_11354_amd import synth
 from tests import gpu_util as G
@@ -143,3 +144,27 @@ def test_values_at_the_ends_of_the_range(oracle, bq, dtype, launch, scales, tail
     err = _error(case, oracle, lab, [(0, i) for i in range(case.Nqb)], launch)
     print(f"bq={bq} {dtype} {launch} {scales} {tail}: {err:.3e}")
     assert err <= 2.0 ** -8                                 # fp16 weights, 2^-11, on sums whose terms cancel to a few times that
+
+
+@pytest.mark.parametrize("bq,launch", [(64, 0), (128, 0), (128, 769)])
+@pytest.mark.parametrize("nkb", [2, 9, 20])
+def test_e4m3_block_scales_cancel(bq, launch, nkb):
+    """Every query sees one key 184 binades above all others: its output is that key's V row, code times block scale.  The weight carries
+    the scale relative to the list's and the row sum has it divided out again: what that leaves is below 2^-15 (two of fp16's roundings
+    in turn, 2^-22, and a few of fp32), where a factor rounded to fp16 would leave up to 2^-12."""
+    rng = np.random.default_rng(nkb)
+    N = nkb * 64
+    of_row = rng.integers(0, 32, N)
+    key = 64 * (np.arange(32) % nkb) + rng.integers(0, 64, 32)
+    q, k = np.zeros((N, 64)), np.zeros((N, 64))
+    q[np.arange(N), of_row] = 32.0
+    k[key, np.arange(32)] = 32.0
+    v = rng.standard_normal((N, 64)) * np.repeat(rng.uniform(0.125, 8.0, nkb), 64)[:, None]
+    case = _case(q, k, v, bq, "fp8")
+    lab = np.full((1, 1, case.Nqb, case.Nkb), 2, np.int8)
+    got = G.sparse_f32(case, lab, launch)
+    codes = torch.from_numpy(case.d["V"][0, 0]).view(torch.float8_e4m3fn).double().numpy()
+    want = (codes * np.repeat(case.d["sV"][0, 0].astype(np.float64), 64)[:, None])[key[of_row]]
+    err = np.abs(got - want).max(axis=1) / np.abs(want).max(axis=1)
+    print(f"bq={bq} {launch} {nkb}: {err.max():.3e}")
+    assert err.max() <= 2.0 ** -15
