@@ -93,6 +93,10 @@ sla_status_t sla_workspace_bytes(const sla_params_t *p, size_t *bytes);
  *   labels    out  optional int8 [B,H,Nqb,Nkb]; NULL to skip
  * A query row with NaN or +infinity among the logits of its critical blocks comes out NaN; it does not affect other rows
  * beyond the block labels, which its block's mean decides.
+ * The same call gives the same bits.  With bq = 128 the last bits of O can depend on B H ceil(N/bq), which decides how
+ * the attention splits its work: a batch and its items one by one agree to rounding.
+ * The V blocks of a row's critical list may differ in magnitude by any factor if the list has at most 64 blocks; in a longer
+ * one, a block behind the first 64 may exceed all of those by up to 2^100 (beyond that their share of the weight is lost).
  */
 sla_status_t sla_forward(const sla_params_t *p,
                          const void *Q, const void *K, const void *V,

@@ -903,11 +903,19 @@ hipError_t launch_transpose_w(const void *W, int nW, void *WT, hipStream_t st)
     return hipGetLastError();
 }
 
-// Whether the keys of a 128-row query block are split between waves as well (four waves, twice the speed per block, half the blocks at
-// a time: 512 where the two-wave form holds 1024).  It pays where the two-wave form would leave slots empty: below three quarters of a
-// round of 1024 and in the first half of a second one (a layer of 16 heads, bf16, split against not: 36 blocks a head 51.8 / 52.4 us,
-// 60: 67.2 / 65.4, 75: 88.4 / 91.1, 94: 110.3 / 113.2, 100: 123.8 / 121.8, 126: 154.9 / 146.8, 150: 202 / 194).
-static bool split_keys(long total) { return total <= 768 || (total > 1024 && total <= 1536); }
+// Whether the keys of a 128-row query block are split between waves as well: four waves, twice the speed per block, two blocks to a CU
+// where the two-wave form has four.  It pays where that saves half a round, in the first half of the two-wave form's first round and of
+// its second; from the third on the dispatch of blocks evens the rounds out.  Layers of 16 heads, split / not, us, bf16 lists of 3 %, 10 % and 20 %
+// of the blocks, then E4M3: 480 blocks 33.1 / 34.5, 38.0 / 41.1, 44.3 / 50.1; 37.0 / 39.1, 40.9 / 44.8, 46.6 / 53.2; 576 blocks 39.6 / 38.3, 46.8 / 45.3,
+// 57.3 / 55.0; 40.8 / 39.4, 46.4 / 45.0, 56.2 / 54.9; 896: 47.8 / 45.2, 63.1 / 59.6, 86.1 / 81.0; 44.5 / 42.5, 58.5 / 55.2, 78.0 / 72.8; 1120: 62.9 / 61.7,
+// 88.0 / 88.4, 125 / 128; 59.7 / 58.9, 81.3 / 82.3, 114 / 117; 1520: 78.6 / 80.3, 120 / 127, 181 / 195; 73.1 / 74.7, 109 / 117, 160 / 173; at 5 %
+// 1552: 101 / 99; 94 / 91; 2400: 177 / 167; 155 / 146.
+// (The two forms add in another order: with 128-row blocks the last bits of a head can depend on how many blocks the launch has.)
+static bool split_keys(long total)
+{
+    constexpr long kSlots = 4 * 256;                       // workgroups of the two-wave form the chip holds
+    return total <= kSlots / 2 || (total > kSlots && total <= 3 * kSlots / 2);
+}
 
 hipError_t launch_attend(const void *Q, const void *K, const void *Vp, const float *lvs,
                          const float *sQ, const float *sK, bool fp8, RowMap rm,

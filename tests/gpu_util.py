@@ -125,7 +125,7 @@ def sparse_f32(case: Case, lab: np.ndarray, launch_blocks: int = 0) -> np.ndarra
 
 
 # (query block, data type, query blocks of the launch) of attend_kernel's forms: 128-row blocks run on four waves in launches of
-# at most 768 blocks and on two waves in launches of 769 to 1024
+# at most 512 blocks and on two waves in launches of 513 to 1024
 ATTEND_FORMS = [(64, "bf16", 0), (64, "fp8", 0), (128, "bf16", 0), (128, "fp8", 0), (128, "bf16", 769), (128, "fp8", 769)]
 
 

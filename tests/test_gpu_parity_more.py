@@ -109,7 +109,7 @@ def test_forward_more_shapes(oracle, name, phi):
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
 def test_two_wave_form_with_the_linear_branch(oracle, dtype):
     """100 heads x 8 query blocks of 128 rows, the last one ragged at a ragged key block: a launch of the two-wave form of the
-    attention kernel (more than 768 blocks), whole forward and given labels with lists of 0 to 5 blocks, a few heads against the oracle."""
+    attention kernel (513 to 1024 blocks), whole forward and given labels with lists of 0 to 5 blocks, a few heads against the oracle."""
     cfg = (C4 if dtype == "fp8" else C0).with_(B=1, H=100, N=901, bq=128, proj_per_head=True)
     case = G.Case(cfg, k_crit=5, k_neg=4)
     rng = np.random.default_rng(9)
