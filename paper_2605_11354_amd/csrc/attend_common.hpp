@@ -14,14 +14,12 @@ typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
 __device__ __forceinline__ int swz8(int row) { return (row >> 1) & 7; }
 __device__ __forceinline__ int swz4(int row) { return (row >> 2) & 3; }
 
-// Waits until at most N of this wave's tile copies are outstanding and its LDS reads have returned, then joins
-// the workgroup.  The copies are issued from inline assembly so that the compiler's own wait-count
+// Waits until this wave's tile copies have landed and its LDS reads have returned, then joins the workgroup.  The copies are issued from inline assembly so that the compiler's own wait-count
 // insertion does not see them: it would otherwise drain ALL outstanding copies (vmcnt(0)) before every LDS read
 // and serialise the prefetch ring.  The waits are therefore explicit.
-template <int N> __device__ __forceinline__ void wait_copies_and_barrier()
+__device__ __forceinline__ void wait_copies_and_barrier()
 {
-    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 __device__ __forceinline__ uint32_t pack_f16(float lo, float hi)
@@ -84,17 +82,7 @@ __device__ __forceinline__ int lane_now()
     return l;
 }
 
-#ifdef SLA_PROBE_TIME   /* timing probe only: cycle counter of one wave at five points of every tile */
-static __device__ unsigned long long sla_wg_times[2 * 32768];      // 100 MHz clock at the start and the end of every workgroup (the first 32768)
-static __device__ unsigned long long sla_probe_times[64 * 8];
-#define SLA_TP(row, pt) do { if (probe_on) { const unsigned long long t_ = __builtin_readcyclecounter(); if (lane == 0) tprobe[(row) * 8 + (pt)] = t_; } } while (0)
-#define SLA_T(c, pt) do { if ((c) < 61) SLA_TP(c, pt); } while (0)      /* rows 61..63: epilogue, prologue, wave life */
-#else
-#define SLA_TP(row, pt)
-#define SLA_T(c, pt)
-#endif
-
-// What both attention kernels take (grid: one workgroup of two waves per query block)
+// What both attention kernels take (grid: one workgroup per query block, of two waves, or four in attend_kernel<., 2, 2>)
 typedef void AttendKernel(const void *__restrict__ Qp, const void *__restrict__ Kp, const uint16_t *__restrict__ Vp, const float *__restrict__ lvs,
                           const float *__restrict__ sQ, const float *__restrict__ sK, RowMap rm, const int32_t *__restrict__ crit_idx, int k_c,
                           const uint16_t *__restrict__ Hq, const uint16_t *__restrict__ WT, int proj_per_head, int phi, int H, int N, int Nqb, int Nkb,

@@ -91,6 +91,16 @@ constexpr float kSpoilt = 12.0f;
 // in fp32 (prescan).
 constexpr float kTinyV = 8.0f;
 
+#ifdef SLA_PROBE_TIME   /* timing probe only: cycle counter of one wave at five points of every tile */
+__device__ unsigned long long sla_wg_times[2 * 32768];      // 100 MHz clock at the start and the end of every workgroup (the first 32768)
+__device__ unsigned long long sla_probe_times[64 * 8];
+#define SLA_TP(row, pt) do { if (probe_on) { const unsigned long long t_ = __builtin_readcyclecounter(); if (lane == 0) tprobe[(row) * 8 + (pt)] = t_; } } while (0)
+#define SLA_T(c, pt) do { if ((c) < 61) SLA_TP(c, pt); } while (0)      /* rows 61..63: epilogue, prologue, wave life */
+#else
+#define SLA_TP(row, pt)
+#define SLA_T(c, pt)
+#endif
+
 // RH row halves of 64 rows times KS parts of the keys: one wave each
 template <bool FP8, int RH, int KS>
 struct AttendTile {
@@ -507,7 +517,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
     // Q, the scales and the first tiles land here, once (a builtin, so that the compiler's bookkeeping sees it)
     __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));
     window_scales(true, lv_first, exp_constant(sk_first));
-    wait_copies_and_barrier<0>();
+    wait_copies_and_barrier();
     SLA_TP(62, 4);
     w[A][0] = w[A][1] = w[B][0] = w[B][1] = __builtin_bit_cast(f16x8, make_uint4(0, 0, 0, 0));
 #pragma unroll
@@ -649,7 +659,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
         constexpr int P = decltype(phase)::value;
         constexpr int vslot = T::VRING + P * T::VBYTES;
         SLA_T(c, 0);
-        wait_copies_and_barrier<0>();
+        wait_copies_and_barrier();
         SLA_T(c, 1);
         const uint32_t j_cur = entry_j(c);
         t_nxt = tile_info(min(c + 1, k - 1));
@@ -694,7 +704,7 @@ __global__ __launch_bounds__(64 * RH * KS, 2) void attend_kernel(
     }
 #undef SLA_SB
 
-    wait_copies_and_barrier<0>();                          // epilogue operands landed; every wave is past its last tile
+    wait_copies_and_barrier();                          // epilogue operands landed; every wave is past its last tile
     const int elane = lane_now(), e32 = elane & 31, eg = elane >> 5;         // (the loop carries no lane index)
     SLA_TP(61, 0);
     l_old[B][0] = lsum[B][0];

@@ -1,7 +1,7 @@
 // attend_kernel's computation (k_attend.hip) for SHORT critical lists (frame attention: one or two blocks per row; up to kShortList), where
 // a workgroup's life is memory latency (list -> tiles, operands of the linear branch) and little arithmetic: no software
-// pipeline and no rings, so that the kernel fits 128 registers and 17 KB of LDS and eight workgroups of two waves (four
-// of four) share a CU and hide each other's round trips.  Order of work: the linear branch first (its operands, the Hq^T
+// pipeline and no rings, so that the kernel fits 128 registers and 17 KB of LDS and eight workgroups of two waves
+// share a CU and hide each other's round trips.  Order of work: the linear branch first (its operands, the Hq^T
 // tile, W^T and Z, are asked for together with Q and the list; its result waits in sixteen registers as bf16), then one
 // tile at a time through a single K slot and a single V^T slot: S^T, exact running maximum, fp16 weights carrying the
 // block's V exponent, O^T += V^T P^T; at the end O = O_sparse / l + O_lin W.
@@ -23,17 +23,14 @@ __device__ __forceinline__ void copy_2k_to_lds(const uint8_t *base0, const uint8
                  "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %4\n\ts_mov_b32 m0, %0"
                  : "=&s"(saved_m0) : "v"(v0), "v"(v1), "s"(base0), "s"(base1), "s"(lds_addr) : "memory", "scc");
 }
-// N such copies of consecutive 1 KB pieces of a tile: piece x starts at base + x stride in memory and takes the per-lane
+// N such copies (an even number) of consecutive 1 KB pieces of a tile: piece x starts at base + x stride in memory and takes the per-lane
 // offset voff, for odd x with bit 6 flipped if FLIP (see CopyOffsets)
 template <int N, bool FLIP> __device__ __forceinline__ void copy_nk_to_lds(const uint8_t *base, uint32_t stride, uint32_t voff, uint32_t lds_addr)
 {
-    static_assert(N == 1 || N == 2 || N == 4, "1, 2 or 4 copies");
-    if constexpr (N == 1) copy_1k_to_lds(base, voff, lds_addr);
-    else {
-        const uint32_t odd = FLIP ? voff ^ 64u : voff;
+    static_assert(N % 2 == 0, "pieces go in pairs");
+    const uint32_t odd = FLIP ? voff ^ 64u : voff;
 #pragma unroll
-        for (int x = 0; x < N; x += 2) copy_2k_to_lds(base + x * stride, base + (x + 1) * stride, voff, odd, lds_addr + x * 1024);
-    }
+    for (int x = 0; x < N; x += 2) copy_2k_to_lds(base + x * stride, base + (x + 1) * stride, voff, odd, lds_addr + x * 1024);
 }
 
 // The row sums are those of the weights with the V scale 2^lsv, divided by it, unless it is further than 2^kFarSum from the list's
@@ -49,12 +46,13 @@ __device__ __forceinline__ float max16(const f32x16 &s)
     return max3(max3(a, b, c), max3(d, e, s[15]), a);
 }
 
-template <int NWAVES, bool FP8>
+constexpr int kWaves = 2;                              // of 32 query rows
+template <bool FP8>
 struct Tile {
     static constexpr int KBYTES = FP8 ? 64 * 64 : 64 * 128;     // K tile (e4m3 / bf16)
     static constexpr int VBYTES = 64 * 128;                     // V^T tile (always fp16)
-    static constexpr int KINS = KBYTES / 1024 / NWAVES;         // 1 KB copy instructions per wave
-    static constexpr int VINS = VBYTES / 1024 / NWAVES;
+    static constexpr int KINS = KBYTES / 1024 / kWaves;         // 1 KB copy instructions per wave
+    static constexpr int VINS = VBYTES / 1024 / kWaves;
 };
 
 // Per-lane byte offset of the 16-byte chunk each lane copies in one 1 KB instruction: LDS position (row, slot) <- global
@@ -62,9 +60,9 @@ struct Tile {
 // which advances the swizzle by 4 ins mod 8 (a flip of offset bit 6 for odd ins) or by 4 ins mod 4 = 0: one register
 // serves all of a wave's copies, the rows themselves are advanced in the scalar base (row pitches are multiples of 128 bytes
 // where the flip is used).
-template <int NWAVES, bool FP8>
+template <bool FP8>
 struct CopyOffsets {
-    using T = Tile<NWAVES, FP8>;
+    using T = Tile<FP8>;
     static constexpr int kRows = FP8 ? 16 : 8;         // K rows per instruction
     uint32_t k, v;
     uint32_t kstride;                                  // bytes from one K instruction's rows to the next's (uniform)
@@ -78,8 +76,6 @@ struct CopyOffsets {
         const uint32_t r = lane >> 3, chunk = (uint32_t)((lane & 7) ^ swz8(r)) << 4;
         v = r * 128u + chunk;
         k = FP8 ? (uint32_t)(lane >> 2) * (uint32_t)krowb + ((uint32_t)((lane & 3) ^ swz4(lane >> 2)) << 4) : r * (uint32_t)krowb + chunk;
-        if constexpr (T::KINS == 1 && !FP8) k ^= (uint32_t)(wave_k & 1) << 6;
-        if constexpr (T::VINS == 1) v ^= (uint32_t)(wave_v & 1) << 6;
     }
     // this wave's share of the K tile at kt / of a contiguous 8 KB tile at vt, to the tile at LDS address dst
     __device__ __forceinline__ void copy_k(const uint8_t *kt, uint32_t dst) const
@@ -104,14 +100,14 @@ struct CopyOffsets {
     }
 };
 
-template <int NW, bool FP8>
-__global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
+template <bool FP8>
+__global__ __launch_bounds__(64 * kWaves, 4) void attend_short_kernel(
     const void *__restrict__ Qp, const void *__restrict__ Kp, const uint16_t *__restrict__ Vp, const float *__restrict__ lvs,
     const float *__restrict__ sQ, const float *__restrict__ sK, RowMap rm,
     const int32_t *__restrict__ crit_idx, int k_c, const uint16_t *__restrict__ Hq, const uint16_t *__restrict__ WT,
     int proj_per_head, int phi, int H, int N, int Nqb, int Nkb, long total, float c_exp, uint16_t *__restrict__ O, float *__restrict__ O32)
 {
-    constexpr int BQ = 32 * NW;
+    constexpr int BQ = 32 * kWaves;
     constexpr int ES = FP8 ? 1 : 2;
     constexpr int KROWB = FP8 ? 64 : 128;
     constexpr int kA = 0, kB = 8192, kZ = 16384;      // LDS: slot A (K tile / Hq^T), slot B (V^T tile / W^T), the Z row
@@ -152,7 +148,7 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
     }
     const float qscale = FP8 ? sQ[work] : 1.0f;
 
-    CopyOffsets<NW, FP8> co;
+    CopyOffsets<FP8> co;
     co.init(__builtin_amdgcn_readfirstlane(wave), lane, krowb);
     const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_void_p)lds;
     const uint32_t ktile_bytes = (uint32_t)kBK * (uint32_t)krowb;
@@ -178,7 +174,7 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
     float lv_ref = 0.f;
     const float d_lv = relative_scale(lv, lane < k, true, lv_ref);
     __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));      // vmcnt(0): Q, the list and the operands have landed
-    wait_copies_and_barrier<0>();
+    wait_copies_and_barrier();
 
     f32x16 zero16;
 #pragma unroll
@@ -264,7 +260,7 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
 #pragma unroll
             for (int y = 0; y < 8; ++y) lin[8 * e + y] = pack_bf16(pl[e][2 * y], pl[e][2 * y + 1]);
     }
-    wait_copies_and_barrier<0>();                      // every wave is done with the operands: the slots take tiles now
+    wait_copies_and_barrier();                      // every wave is done with the operands: the slots take tiles now
     auto request_tile = [&](int c) __attribute__((always_inline)) {
         const uint32_t j = (uint32_t)__builtin_amdgcn_readlane(d_j, c);
         const uint8_t *kt = Kh + (uint64_t)j * ktile_bytes;
@@ -291,7 +287,7 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
         const float lsv = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(d_lv), c));
         const bool far = !(fabsf(lsv) <= kFarSum);     // then the weights are summed without the V scale
         const float per_scale = far ? 0.f : fast_exp2(-lsv);
-        wait_copies_and_barrier<0>();                  // tile c has landed
+        wait_copies_and_barrier();                  // tile c has landed
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             f32x16 sacc;
@@ -354,7 +350,7 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
                     oacc[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, p[ss], oacc[e], 0, 0, 0);
                 }
         }
-        wait_copies_and_barrier<0>();                  // all waves are done with the tile before the next one is asked for
+        wait_copies_and_barrier();                  // all waves are done with the tile before the next one is asked for
     }
 
     // ---- O = O_sparse / l + O_lin W
@@ -377,7 +373,7 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
                         make_float4(oacc[e][4 * aa + 0], oacc[e][4 * aa + 1], oacc[e][4 * aa + 2], oacc[e][4 * aa + 3]);
         }
     } else {
-        uint8_t *ot = lds + wave * 4096;               // (NW x 4 KB: inside the two slots)
+        uint8_t *ot = lds + wave * 4096;               // (inside the two slots)
         const int f = ((l32 >> 1) & 7) << 1;
 #pragma unroll
         for (int e = 0; e < 2; ++e)
@@ -401,6 +397,6 @@ __global__ __launch_bounds__(64 * NW, 4) void attend_short_kernel(
     }
 }
 
-AttendKernel *attend_short_kernel_for(bool fp8) { return fp8 ? attend_short_kernel<2, true> : attend_short_kernel<2, false>; }
+AttendKernel *attend_short_kernel_for(bool fp8) { return fp8 ? attend_short_kernel<true> : attend_short_kernel<false>; }
 
 }  // namespace sla
