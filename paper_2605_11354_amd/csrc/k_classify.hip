@@ -716,7 +716,10 @@ __global__ __launch_bounds__(64) void select_kernel(const double *__restrict__ S
 // the LDS reads of the chains.  Staged by channels, a read of the Q mean serves all the lane's chains (KPL + 1 reads for KPL
 // chains where 64 key blocks at a time needed 2 KPL) and the chains run side by side; with both ranks of the
 // classification in one descent (classify_row_wave) 16 heads x 172 rows of 172 key blocks: 15.2 -> 13.5 us (0.3 of it the
-// descent).  Eight channels at a time: 14.9 (twice the barriers).  Q through LDS as whole rows, as for shorter rows:
+// descent).  The other forms, before and now (the classifier between two events, some 4 us of which are the events): two keys a lane, 16 heads
+// of 100 blocks 12.3 -> 11.6, e4m3 12.3 -> 11.7, 128 of 128 rows 11.6 -> 11.4; four keys a lane, which take 48 KB of LDS and 131 registers, three
+// workgroups to a CU instead of four: 200 blocks 23.4 -> 21.6, 250 22.7 -> 22.2, 256 of 128 rows 19.0 -> 17.4, e4m3 17.2 -> 16.0, 4 heads of
+// 256 14.2 -> 12.2.  Eight channels at a time: 14.9 (twice the barriers).  Q through LDS as whole rows, as for shorter rows:
 // 15.0 (its round trips are in series with the rest).
 template <int KPL, bool FP8>
 __global__ __launch_bounds__(256, KPL == 4 ? 3 : 4) void classify_fused_kernel(const void *__restrict__ Q, const float *__restrict__ sQ, RowMap rm,
