@@ -37,7 +37,7 @@
 // unit from the fp16 weights), two instructions a unit; then the unit is repaired (see there).  A maximum over the exponents in front of
 // the exponentials, the form before, takes ten of the unit's 52 vector instructions, and vector issue is what bounds the loop.
 // A repair reads its keys again from global memory, some 4000 cycles with the wait of the other waves, so the tiles behind one are
-// prescanned (see there): where a logit has left the range another is likely to, and the maximum in front of them costs a tenth of that.
+// prescanned (see there): where a logit has left the range another is likely to, and a prescan costs some 1350 a tile, raise included.
 // Tiles whose V scale is far from the list's are prescanned too, for their row sums.  Forward on given labels with 16 heads, against a repair
 // for every unit that passes 2^8 or is of such a tile: 43968 tokens, V of every second block 2^-10 of the others' 1270 -> 805 us; one
 // block in sixteen 752 -> 617; keys four times as long 674 -> 601, ten times 854 -> 676, growing along the sequence by twenty 1264 -> 720;
@@ -63,7 +63,7 @@
 // then W^T x O_lin^T, added to the normalised sparse output and stored as bf16.
 //
 // What bounds it: the issue of vector instructions beside the MFMA (42 and 10 per unit), LDS reads and tile copies, each about a tenth
-// of the time (left out one at a time), prologue and epilogue (a tenth on lists of 34, half on lists of 9).  Against 32 rows per wave
+// of the time (left out one at a time), prologue and epilogue (a sixth on lists of 34, over 40 % on lists of 9).  Against 32 rows per wave
 // with a maximum over the exponents and a separate careful form of a step, launches of 16 heads: 43968 tokens, lists of 34, bf16 497 ->
 // 420 us; 137400 tokens, lists of 64, e4m3 2300 -> 1960; 17856 tokens, lists of 14, bf16 106 -> 96; 10992 tokens in 64-row blocks, lists
 // of 9, 58.5 -> 55.5.  Of that, 64 rows per wave and buffer copies (a third of the scalar instructions) gave 9 %, the check on the row
